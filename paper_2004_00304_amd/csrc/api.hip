@@ -8,7 +8,6 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
-#include <mutex>
 #include <new>
 #include <string>
 #include <vector>
@@ -19,12 +18,6 @@
 #include "launch.hpp"
 
 using namespace lbmpcd;
-
-// Activations of lbmpcd_closure_forward_noalloc: a file-scope device array, one
-// copy on every device the library runs on, held until the process ends.  In
-// host code this name is only a stand-in for the symbol; the device address of
-// each copy comes from hipGetSymbolAddress (noalloc_scratch below).
-static __device__ __align__(256) unsigned char scratch[closure_fwd_bytes(LBMPCD_NOALLOC_MAX_ROWS)];
 
 struct lbmpcd_ctx {
     int n_inst = 0, dim = 2, lb_fp = 64, part_fp = 64, S = 1, Q = 9, mpcd = 0;
@@ -87,8 +80,7 @@ struct lbmpcd_ctx {
     // learned closure (channel 0)
     bool closure = false;          // region reserved
     float* cl_P = nullptr;         // [NPARAM] FP32 parameters
-    uint16_t* cl_Pb = nullptr;     // [NPARAM] BF16 copy
-    uint16_t* cl_Pf = nullptr;     // [NFRAG] BF16 weights in the fused kernel's fragment order
+    uint16_t* cl_Pf = nullptr;     // [NFRAG] BF16 weights in fragment order, follow every change of cl_P
     float* cl_G = nullptr;         // [NPARAM] gradient
     float* cl_m = nullptr;         // [NPARAM] Adam first moment
     float* cl_v = nullptr;         // [NPARAM] Adam second moment
@@ -98,7 +90,8 @@ struct lbmpcd_ctx {
     double* cl_facc = nullptr;     // [nslab][NF] feature sums of a collection window
     double* cl_nm = nullptr;       // [nslab][10] particle moment sums
     float* cl_uc = nullptr;        // [nslab][3] LB velocity of each slab node (surrogate step)
-    ClosureBufs cl_inf;            // inference activations, one row per slab node
+    float* cl_M = nullptr;         // [band nodes][12] moments and shear rate (surrogate step)
+    float* cl_Y = nullptr;         // [nslab][NOUT] standardised network output (surrogate step)
     long long cl_nslab = 0;
     bool cl_ready = false;         // parameters and statistics set
     bool cl_collect = false;       // collection window: features after every LB collide-stream
@@ -116,32 +109,6 @@ thread_local std::string g_err;
 int fail(lbmpcd_ctx* c, int code, const std::string& msg) {
     if (c) c->err = msg; else g_err = msg;
     return code;
-}
-
-// Device address of the `scratch` array on each device, resolved once per
-// device (with that device current) at lbmpcd_init.
-constexpr int MAX_DEVICES = 64;
-std::mutex g_scratch_mu;
-void* g_scratch_ptr[MAX_DEVICES] = {};
-
-int resolve_noalloc_scratch(int device, std::string& msg) {
-    if (device < 0 || device >= MAX_DEVICES) { msg = "device index beyond the library's table"; return LBMPCD_E_DEVICE; }
-    std::lock_guard<std::mutex> lock(g_scratch_mu);
-    if (g_scratch_ptr[device]) return 0;
-    void* p = nullptr;
-    const hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
-    if (e != hipSuccess || !p) {
-        msg = std::string("hipGetSymbolAddress(scratch): ") + hipGetErrorString(e);
-        return LBMPCD_E_DEVICE;
-    }
-    g_scratch_ptr[device] = p;
-    return 0;
-}
-
-void* noalloc_scratch(int device) {
-    if (device < 0 || device >= MAX_DEVICES) return nullptr;
-    std::lock_guard<std::mutex> lock(g_scratch_mu);
-    return g_scratch_ptr[device];
 }
 
 #define HIPCHK(ctx, expr)                                                                          \
@@ -382,7 +349,7 @@ static int default_wg_threads(int part_fp, int cap_max, int exp_max, long long t
 
 struct Layout {
     size_t desc, tile_inst, f0, f1, ub, uf, tb, tf, acc, fbu, prof, fill0, fill1, stats, ovf, clock, shifts, scratch, end;
-    size_t cl_P, cl_Pb, cl_Pf, cl_G, cl_m, cl_v, cl_stats, cl_sums, cl_loss, cl_facc, cl_nm, cl_uc, cl_inf;
+    size_t cl_P, cl_Pf, cl_G, cl_m, cl_v, cl_stats, cl_sums, cl_loss, cl_facc, cl_nm, cl_uc, cl_M, cl_Y;
     size_t part[2];       // particle buffer: 2 dim component arrays of cstride bytes, then ids
     size_t cstride;
     size_t acc_bytes, prof_bytes, scratch_bytes;
@@ -478,7 +445,6 @@ int build(const lbmpcd_params* p, int n, std::vector<InstDesc>& D, Layout& L, lo
     L.scratch = take(L.scratch_bytes);
     if (p[0].closure) {
         L.cl_P = take(4 * (size_t)NPARAM);
-        L.cl_Pb = take(2 * (size_t)NPARAM);
         L.cl_Pf = take(2 * (size_t)NFRAG);
         L.cl_G = take(4 * (size_t)NPARAM);
         L.cl_m = take(4 * (size_t)NPARAM);
@@ -489,7 +455,8 @@ int build(const lbmpcd_params* p, int n, std::vector<InstDesc>& D, Layout& L, lo
         L.cl_facc = take(8 * (size_t)slab * NF);
         L.cl_nm = take(8 * (size_t)slab * 10);
         L.cl_uc = take(4 * (size_t)slab * 3);
-        L.cl_inf = take(closure_bufs_bytes(slab, false));
+        L.cl_M = take(4 * (size_t)band * BMS);
+        L.cl_Y = take(4 * (size_t)slab * NOUT);
     }
     L.end = o;
     return 0;
@@ -678,7 +645,6 @@ int lbmpcd_init(const lbmpcd_params* p, int32_t n_inst, void* dev_workspace, siz
     c->Q = c->dim == 2 ? 9 : 19; c->mpcd = p[0].mpcd;
     c->stream = (hipStream_t)hip_stream;
     if (hipGetDevice(&c->device) != hipSuccess) { delete c; return fail(nullptr, LBMPCD_E_DEVICE, "no HIP device"); }
-    if (int se = resolve_noalloc_scratch(c->device, msg)) { delete c; return fail(nullptr, se, msg); }
     c->ws = (char*)dev_workspace;
     c->ws_bytes = bytes;
     c->total_nodes = tot[0]; c->total_band = tot[1]; c->total_ufine = tot[2]; c->total_tiles = tot[3];
@@ -717,7 +683,6 @@ int lbmpcd_init(const lbmpcd_params* p, int32_t n_inst, void* dev_workspace, siz
     if (p[0].closure) {
         c->closure = true;
         c->cl_P = (float*)(c->ws + L.cl_P);
-        c->cl_Pb = (uint16_t*)(c->ws + L.cl_Pb);
         c->cl_Pf = (uint16_t*)(c->ws + L.cl_Pf);
         c->cl_G = (float*)(c->ws + L.cl_G);
         c->cl_m = (float*)(c->ws + L.cl_m);
@@ -729,7 +694,8 @@ int lbmpcd_init(const lbmpcd_params* p, int32_t n_inst, void* dev_workspace, siz
         c->cl_nm = (double*)(c->ws + L.cl_nm);
         c->cl_uc = (float*)(c->ws + L.cl_uc);
         c->cl_nslab = c->desc[0].nslab;
-        closure_bufs_carve((unsigned char*)(c->ws + L.cl_inf), c->cl_nslab, false, c->cl_inf);
+        c->cl_M = (float*)(c->ws + L.cl_M);
+        c->cl_Y = (float*)(c->ws + L.cl_Y);
     }
     c->scratch = c->ws + L.scratch;
     c->scratch_bytes = L.scratch_bytes;
@@ -795,15 +761,13 @@ namespace {
 
 // Enqueue one coupled LB step on stream s (the context's stream, or the
 // capture stream while a graph is recorded).
-// The network's standardised output (cl_inf.Y) and the nodes' LB velocities
-// (cl_uc) for the current populations, by the fused inference kernel.  The
-// band moments it needs overlay the feature buffer of the separate products.
+// The network's standardised output (cl_Y) and the nodes' LB velocities
+// (cl_uc) for the current populations, by the fused inference kernel.
 static hipError_t closure_predict_now(lbmpcd_ctx* c, hipStream_t s) {
     const InstDesc& d = c->desc[0];
     const long long nband = (long long)d.nx * d.nyb * d.nz;
     return closure_predict(c->lb_fp, c->d_desc, 0, c->cl_nslab, nband, d.by0, d.nyb, c->f[c->fcur],
-                           (float*)c->cl_inf.X, c->cl_stats, c->cl_Pb, c->cl_Pf, c->cl_P, c->cl_inf.Y,
-                           c->cl_uc, s);
+                           c->cl_M, c->cl_stats, c->cl_Pf, c->cl_P, c->cl_Y, c->cl_uc, s);
 }
 
 int enqueue_one_step(lbmpcd_ctx* c, hipStream_t s) {
@@ -820,7 +784,7 @@ int enqueue_one_step(lbmpcd_ctx* c, hipStream_t s) {
             HIPCHK(c, timed(c, 4, [&] {
                        hipError_t e = closure_predict_now(c, s);
                        if (e == hipSuccess)
-                           e = closure_to_acc(c->d_desc, 0, c->cl_nslab, c->cl_inf.Y, c->cl_stats, c->cl_uc, c->acc,
+                           e = closure_to_acc(c->d_desc, 0, c->cl_nslab, c->cl_Y, c->cl_stats, c->cl_uc, c->acc,
                                               c->prof, c->sampling ? 1 : 0, s);
                        return e;
                    }));
@@ -1265,18 +1229,10 @@ int need_closure(lbmpcd_ctx* c) {
     return 0;
 }
 
-size_t train_scratch_bytes(long long rows) {
-    return closure_bufs_bytes(rows, true) + align_up((size_t)rows * NOUT * 4, 256);
-}
-
-// One standardised batch of `rows` rows (drawn, or the first rows of X, Y).
-int closure_batch(lbmpcd_ctx* c, const float* X, const float* Y, long long n, long long rows, bool draw,
-                  uint32_t step, void* scratch, ClosureBufs& b, float*& Yb) {
-    closure_bufs_carve((unsigned char*)scratch, rows, true, b);
-    Yb = (float*)((unsigned char*)scratch + closure_bufs_bytes(rows, true));
+// A batch of `rows` rows of X, Y (drawn, or the first ones) with the context's parameters.
+NetBatch net_batch(lbmpcd_ctx* c, const float* X, const float* Y, long long n, long long rows, bool draw, uint32_t step) {
     const InstDesc& d = c->desc[0];
-    HIPCHK(c, mlp_gather(X, Y, n, c->cl_stats, rows, draw, d.key0, d.key1, step, b.X, Yb, c->stream));
-    return 0;
+    return NetBatch{X, Y, c->cl_stats, c->cl_Pf, c->cl_P, n, rows, draw, d.key0, d.key1, step};
 }
 
 }  // namespace
@@ -1284,7 +1240,7 @@ int closure_batch(lbmpcd_ctx* c, const float* X, const float* Y, long long n, lo
 int lbmpcd_closure_scratch_size(int64_t n, int32_t batch, size_t* bytes) {
     if (!bytes || n < 1) return fail(nullptr, LBMPCD_E_INVALID, "bad arguments");
     const long long rows = batch > 0 && batch < n ? batch : n;
-    *bytes = train_scratch_bytes(rows);
+    *bytes = train_bytes(rows);
     return 0;
 }
 
@@ -1328,13 +1284,13 @@ int lbmpcd_closure_train(lbmpcd_ctx* c, const float* X, const float* Y, int64_t 
     if (!o || o->struct_size != sizeof(lbmpcd_train_opts)) return fail(c, LBMPCD_E_INVALID, "bad train options");
     if (!X || !Y || n < 1 || o->epochs < 1 || !(o->lr > 0.0f)) return fail(c, LBMPCD_E_INVALID, "bad arguments");
     const long long rows = o->batch > 0 && o->batch < n ? o->batch : n;
-    if (!scratch || scratch_bytes < train_scratch_bytes(rows))
+    if (!scratch || scratch_bytes < train_bytes(rows))
         return fail(c, LBMPCD_E_NOMEM, "scratch smaller than lbmpcd_closure_scratch_size");
     hipStream_t s = c->stream;
     if (!c->cl_ready) {
         HIPCHK(c, mlp_stats(X, Y, n, c->cl_sums, c->cl_stats, s));
         const uint32_t k0 = (uint32_t)(o->seed & 0xFFFFFFFFu), k1 = (uint32_t)(o->seed >> 32);
-        HIPCHK(c, mlp_init(c->cl_P, c->cl_Pb, c->cl_m, c->cl_v, k0, k1, s));
+        HIPCHK(c, mlp_init(c->cl_P, c->cl_Pf, c->cl_m, c->cl_v, k0, k1, s));
         c->cl_adam_t = 0;
         c->cl_ready = true;
     }
@@ -1342,15 +1298,10 @@ int lbmpcd_closure_train(lbmpcd_ctx* c, const float* X, const float* Y, int64_t 
     for (int ep = 0; ep < o->epochs; ++ep) {
         HIPCHK(c, hipMemsetAsync(c->cl_loss, 0, sizeof(double), s));
         for (long long st = 0; st < steps; ++st) {
-            ClosureBufs b;
-            float* Yb = nullptr;
-            if (int e = closure_batch(c, X, Y, n, rows, rows < n, (uint32_t)(c->cl_adam_t + 1), scratch, b, Yb))
-                return e;
-            HIPCHK(c, mlp_forward(c->cl_P, c->cl_Pb, b, s));
-            HIPCHK(c, mlp_backward(c->cl_Pb, Yb, b, c->cl_G, c->cl_loss, s));
             ++c->cl_adam_t;
-            HIPCHK(c, mlp_adam(c->cl_P, c->cl_Pb, c->cl_G, c->cl_m, c->cl_v, c->cl_adam_t, o->lr, o->beta1,
-                               o->beta2, o->eps, s));
+            const AdamState adam{c->cl_P, c->cl_m, c->cl_v, c->cl_Pf, c->cl_adam_t, o->lr, o->beta1, o->beta2, o->eps};
+            HIPCHK(c, net_gradient(net_batch(c, X, Y, n, rows, rows < n, (uint32_t)c->cl_adam_t), scratch, nullptr, &adam,
+                                   c->cl_loss, s));
         }
         if (loss_per_epoch) {
             double l = 0.0;
@@ -1367,15 +1318,11 @@ int lbmpcd_closure_loss_grad(lbmpcd_ctx* c, const float* X, const float* Y, int6
     if (int e = need_closure(c)) return e;
     if (!c->cl_ready) return fail(c, LBMPCD_E_STATE, "closure parameters are not set");
     if (!X || !Y || n < 1) return fail(c, LBMPCD_E_INVALID, "bad arguments");
-    if (!scratch || scratch_bytes < train_scratch_bytes(n))
+    if (!scratch || scratch_bytes < train_bytes(n))
         return fail(c, LBMPCD_E_NOMEM, "scratch smaller than lbmpcd_closure_scratch_size(n, n)");
     hipStream_t s = c->stream;
-    ClosureBufs b;
-    float* Yb = nullptr;
-    if (int e = closure_batch(c, X, Y, n, n, false, 0u, scratch, b, Yb)) return e;
     HIPCHK(c, hipMemsetAsync(c->cl_loss, 0, sizeof(double), s));
-    HIPCHK(c, mlp_forward(c->cl_P, c->cl_Pb, b, s));
-    HIPCHK(c, mlp_backward(c->cl_Pb, Yb, b, c->cl_G, c->cl_loss, s));
+    HIPCHK(c, net_gradient(net_batch(c, X, Y, n, n, false, 0u), scratch, c->cl_G, nullptr, c->cl_loss, s));
     if (loss) HIPCHK(c, hipMemcpyAsync(loss, c->cl_loss, sizeof(double), hipMemcpyDeviceToHost, s));
     if (grad) HIPCHK(c, hipMemcpyAsync(grad, c->cl_G, sizeof(float) * NPARAM, hipMemcpyDeviceToHost, s));
     HIPCHK(c, hipStreamSynchronize(s));
@@ -1386,13 +1333,9 @@ int lbmpcd_closure_forward(lbmpcd_ctx* c, const float* X, int64_t n, float* Y, v
     if (int e = need_closure(c)) return e;
     if (!c->cl_ready) return fail(c, LBMPCD_E_STATE, "closure parameters are not set");
     if (!X || !Y || n < 1) return fail(c, LBMPCD_E_INVALID, "bad arguments");
-    if (!scratch || scratch_bytes < train_scratch_bytes(n))
+    if (!scratch || scratch_bytes < train_bytes(n))
         return fail(c, LBMPCD_E_NOMEM, "scratch smaller than lbmpcd_closure_scratch_size(n, n)");
-    ClosureBufs b;
-    float* Yb = nullptr;
-    if (int e = closure_batch(c, X, nullptr, n, n, false, 0u, scratch, b, Yb)) return e;
-    HIPCHK(c, mlp_forward(c->cl_P, c->cl_Pb, b, c->stream));
-    HIPCHK(c, mlp_destandardize(b.Y, c->cl_stats, X, n, Y, c->stream));
+    HIPCHK(c, net_forward(X, n, c->cl_stats, c->cl_Pf, c->cl_P, Y, c->stream));
     return 0;
 }
 
@@ -1403,14 +1346,7 @@ int lbmpcd_closure_forward_noalloc(lbmpcd_ctx* c, const float* X, int64_t n, flo
     if (n > LBMPCD_NOALLOC_MAX_ROWS)
         return fail(c, LBMPCD_E_INVALID, "n exceeds LBMPCD_NOALLOC_MAX_ROWS (" +
                                              std::to_string(LBMPCD_NOALLOC_MAX_ROWS) + ") rows; split the call");
-    void* ptr = noalloc_scratch(c->device);
-    if (!ptr) return fail(c, LBMPCD_E_STATE, "the device's scratch array was not resolved at lbmpcd_init");
-    ClosureBufs b;
-    closure_bufs_carve((unsigned char*)ptr, n, false, b);
-    const InstDesc& d = c->desc[0];
-    HIPCHK(c, mlp_gather(X, nullptr, n, c->cl_stats, n, false, d.key0, d.key1, 0u, b.X, nullptr, c->stream));
-    HIPCHK(c, mlp_forward(c->cl_P, c->cl_Pb, b, c->stream));
-    HIPCHK(c, mlp_destandardize(b.Y, c->cl_stats, X, n, Y, c->stream));
+    HIPCHK(c, net_forward(X, n, c->cl_stats, c->cl_Pf, c->cl_P, Y, c->stream));
     return 0;
 }
 
@@ -1419,7 +1355,7 @@ int lbmpcd_closure_predict(lbmpcd_ctx* c, float* Y) {
     if (!c->cl_ready) return fail(c, LBMPCD_E_STATE, "closure parameters are not set");
     if (!Y) return fail(c, LBMPCD_E_INVALID, "Y is null");
     HIPCHK(c, closure_predict_now(c, c->stream));
-    HIPCHK(c, mlp_destandardize_uc(c->cl_inf.Y, c->cl_stats, c->cl_uc, c->cl_nslab, Y, c->stream));
+    HIPCHK(c, mlp_destandardize_uc(c->cl_Y, c->cl_stats, c->cl_uc, c->cl_nslab, Y, c->stream));
     return 0;
 }
 
@@ -1436,7 +1372,7 @@ int lbmpcd_closure_weights(lbmpcd_ctx* c, int32_t get_or_set, float* buf, size_t
     } else if (get_or_set == 1) {
         HIPCHK(c, hipMemcpyAsync(c->cl_P, buf, sizeof(float) * NPARAM, hipMemcpyHostToDevice, s));
         HIPCHK(c, hipMemcpyAsync(c->cl_stats, buf + NPARAM, sizeof(float) * NSTATS, hipMemcpyHostToDevice, s));
-        HIPCHK(c, mlp_refresh_bf16(c->cl_P, c->cl_Pb, s));
+        HIPCHK(c, mlp_refresh(c->cl_P, c->cl_Pf, s));
         HIPCHK(c, hipMemsetAsync(c->cl_m, 0, sizeof(float) * NPARAM, s));
         HIPCHK(c, hipMemsetAsync(c->cl_v, 0, sizeof(float) * NPARAM, s));
         HIPCHK(c, hipStreamSynchronize(s));
@@ -1483,7 +1419,7 @@ int lbmpcd_closure_check(lbmpcd_ctx* c, int32_t burst_steps, double* rel_err) {
     HIPCHK(c, launch_zero(c->prof, c->prof_bytes, c->stream));
     HIPCHK(c, closure_predict_now(c, c->stream));
     // written into the sample sums and profile; the sums are cleared again below
-    HIPCHK(c, closure_to_acc(c->d_desc, 0, c->cl_nslab, c->cl_inf.Y, c->cl_stats, c->cl_uc, c->acc, c->prof, 1,
+    HIPCHK(c, closure_to_acc(c->d_desc, 0, c->cl_nslab, c->cl_Y, c->cl_stats, c->cl_uc, c->acc, c->prof, 1,
                              c->stream));
     if (int e = lbmpcd_moments(c, LBMPCD_PROFILE, 0, pp.data(), pp.size() * 8, 0)) return e;
     HIPCHK(c, launch_zero(c->acc, c->acc_bytes, c->stream));
@@ -1530,10 +1466,7 @@ int lbmpcd_closure_gemm_bf16(int64_t M, int64_t N, int64_t K, const uint16_t* A,
     if (M < 0 || N < 0 || K < 1 || !A || !B || !C) return fail(nullptr, LBMPCD_E_INVALID, "bad arguments");
     GemmArgs g{};
     g.M = M; g.N = N; g.K = K;
-    g.A = A; g.sam = K; g.sak = 1;
-    g.B = B; g.sbk = 1; g.sbn = K;
-    g.C = C; g.ldc = N;
-    g.epi = EPI_NONE;
+    g.A = A; g.B = B; g.C = C;
     const hipError_t e = launch_gemm(g, (hipStream_t)hip_stream);
     if (e != hipSuccess) return fail(nullptr, LBMPCD_E_DEVICE, hipGetErrorString(e));
     return 0;

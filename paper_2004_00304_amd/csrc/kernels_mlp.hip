@@ -1,14 +1,13 @@
 // kernels_mlp.hip -- the learned closure's network on gfx950 matrix cores.
 //
-// Dense layers of a small MLP (271 -> 128 -> 128 -> 128 -> 9, GELU) run as
-// BF16 x BF16 -> FP32 products on the MFMA units (v_mfma_f32_32x32x8_bf16):
-// one 64x64 output tile per workgroup, each of its four waves owning a
-// 32x32 quarter.  Operands are read through LDS with arbitrary strides, so
-// one kernel serves the forward product X W^T, the input gradient dZ W and
-// the weight gradient dZ^T X of back-propagation.  The epilogue adds the
-// bias, stores the pre-activation, applies GELU or multiplies by GELU' of
-// the previous layer's pre-activation, and rounds to BF16 where the next
-// product needs it.
+// The dense layers of a small MLP (271 -> 128 -> 128 -> 128 -> 9, GELU) run as
+// BF16 x BF16 -> FP32 products on the MFMA units (v_mfma_f32_32x32x16_bf16).
+// k_net takes a tile of rows through the whole network in one workgroup; in
+// training it goes on through the loss and back to the gradient of the first
+// layer's pre-activation, k_dw forms the weight gradients as a contraction
+// over the rows, split so that it fills the chip, and k_reduce sums the
+// splits and applies Adam: three launches per optimiser step.  k_gemm is the
+// plain product on its own.
 #include <hip/hip_runtime.h>
 
 #include "common.hpp"
@@ -24,13 +23,18 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // BF16 with round-to-nearest-even: gfx950's conversion instruction
 // (v_cvt_pk_bf16_f32); NaN stays NaN.
 __device__ __forceinline__ uint16_t to_bf16(float x) { return __builtin_bit_cast(uint16_t, (__bf16)x); }
-__device__ __forceinline__ float from_bf16(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
+__device__ __forceinline__ f32x16 mfma16(const uint4& a, const uint4& b, f32x16 c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0,
+                                                   0);
+}
 
 constexpr int GT = 64;   // output tile side
 constexpr int GK = 32;   // K step
 constexpr int GKP = GK + 8;  // LDS row pitch (bf16), breaks bank conflicts
 
+// C[M][N] = A[M][K] B[N][K]^T: one 64x64 output tile per workgroup, each of
+// its four waves owning a 32x32 quarter.
 __global__ void __launch_bounds__(256) k_gemm(GemmArgs g) {
     __shared__ uint16_t As[GT][GKP];  // [m][k]
     __shared__ uint16_t Bs[GT][GKP];  // [n][k]
@@ -42,17 +46,11 @@ __global__ void __launch_bounds__(256) k_gemm(GemmArgs g) {
     for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
 
     for (long long k0 = 0; k0 < g.K; k0 += GK) {
-        // operand tiles to LDS, 8 elements per thread per operand; the
-        // thread-to-element map follows whichever stride is unit
         for (int e = tid; e < GT * GK; e += 256) {
-            int m, k;
-            if (g.sak == 1) { m = e / GK; k = e % GK; } else { m = e % GT; k = e / GT; }
-            const long long gm = m0 + m, gk = k0 + k;
-            As[m][k] = (gm < g.M && gk < g.K) ? g.A[gm * g.sam + gk * g.sak] : (uint16_t)0;
-            int n, kb;
-            if (g.sbk == 1) { n = e / GK; kb = e % GK; } else { n = e % GT; kb = e / GT; }
-            const long long gn = n0 + n, gkb = k0 + kb;
-            Bs[n][kb] = (gn < g.N && gkb < g.K) ? g.B[gkb * g.sbk + gn * g.sbn] : (uint16_t)0;
+            const int m = e / GK, k = e % GK;
+            const long long gm = m0 + m, gn = n0 + m, gk = k0 + k;
+            As[m][k] = (gm < g.M && gk < g.K) ? g.A[gm * g.K + gk] : (uint16_t)0;
+            Bs[m][k] = (gn < g.N && gk < g.K) ? g.B[gn * g.K + gk] : (uint16_t)0;
         }
         __syncthreads();
 #pragma unroll
@@ -73,22 +71,14 @@ __global__ void __launch_bounds__(256) k_gemm(GemmArgs g) {
         __syncthreads();
     }
 
-    // epilogue: lane holds column (lane & 31) of its quarter, rows
+    // lane holds column (lane & 31) of its quarter, rows
     // 8 (r / 4) + 4 (lane / 32) + r % 4 for r = 0..15
     const long long col = n0 + wn * 32 + (lane & 31);
     if (col >= g.N) return;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
         const long long row = m0 + wm * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        if (row >= g.M) continue;
-        float v = acc[r];
-        if (g.beta != 0.0f) v += g.beta * g.C[row * g.ldc + col];
-        if (g.bias) v += g.bias[col];
-        if (g.Z) g.Z[row * g.ldz + col] = v;
-        if (g.epi == EPI_GELU) v = gelu(v);
-        else if (g.epi == EPI_GELU_GRAD) v *= gelu_grad(g.Zprev[row * g.ldzp + col]);
-        if (g.C) g.C[row * g.ldc + col] = v;
-        if (g.Cb) g.Cb[row * g.ldcb + col] = to_bf16(v);
+        if (row < g.M) g.C[row * g.N + col] = acc[r];
     }
 }
 
@@ -100,171 +90,477 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
 }
 
 // ---------------------------------------------------------------------------
-// network passes
+// weights in fragment order
 // ---------------------------------------------------------------------------
 static inline unsigned nblk(long long n, int t = 256) { return (unsigned)((n + t - 1) / t); }
 
-size_t closure_bufs_bytes(long long rows, bool backward) {
-    auto al = closure_al256;
-    size_t b = closure_fwd_bytes(rows);
-    if (backward) b += al((size_t)rows * NOUT * 4) + al((size_t)rows * NOUT * 2) +
-                       3 * (al((size_t)rows * NH * 4) + al((size_t)rows * NH * 2));
-    return b;
+// Place of element (k, n) of a B operand of ncb 32-column blocks in fragment
+// order: lane t of a wave holds column t % 32 and k values 8 (t / 32) + j.
+__device__ __forceinline__ long long frag_pos(int ncb, int k, int n) {
+    return ((((long long)(k >> 4) * ncb + (n >> 5)) * 64 + (n & 31) + 32 * ((k >> 3) & 1)) << 3) + (k & 7);
 }
 
-void closure_bufs_carve(unsigned char* base, long long rows, bool backward, ClosureBufs& b) {
-    auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
-    size_t o = 0;
-    auto take = [&](size_t bytes) { unsigned char* p = base + o; o += al(bytes); return p; };
-    b = ClosureBufs{};
-    b.rows = rows;
-    b.X = (uint16_t*)take((size_t)rows * NFP * 2);
-    for (int l = 0; l < 3; ++l) {
-        b.Z[l] = (float*)take((size_t)rows * NH * 4);
-        b.H[l] = (uint16_t*)take((size_t)rows * NH * 2);
-    }
-    b.Y = (float*)take((size_t)rows * NOUT * 4);
-    if (backward) {
-        b.dY = (float*)take((size_t)rows * NOUT * 4);
-        b.dYb = (uint16_t*)take((size_t)rows * NOUT * 2);
-        for (int l = 0; l < 3; ++l) {
-            b.dZ[l] = (float*)take((size_t)rows * NH * 4);
-            b.dZb[l] = (uint16_t*)take((size_t)rows * NH * 2);
-        }
+// Writes parameter i's BF16 value to its places in the fragment arrays (none
+// for a bias).
+__device__ __forceinline__ void frag_store(uint16_t* Pf, long long i, uint16_t v) {
+    if (i < OFF_B1) {
+        const int o = (int)(i / NFP), c = (int)(i % NFP);
+        Pf[FRAG_L1 + frag_pos(4, c, o)] = v;
+    } else if (i >= OFF_W2 && i < OFF_B2) {
+        const int o = (int)((i - OFF_W2) / NH), c = (int)((i - OFF_W2) % NH);
+        Pf[FRAG_L2 + frag_pos(4, c, o)] = v;
+        Pf[TFRAG_L2 + frag_pos(4, o, c)] = v;
+    } else if (i >= OFF_W3 && i < OFF_B3) {
+        const int o = (int)((i - OFF_W3) / NH), c = (int)((i - OFF_W3) % NH);
+        Pf[FRAG_L3 + frag_pos(4, c, o)] = v;
+        Pf[TFRAG_L3 + frag_pos(4, o, c)] = v;
+    } else if (i >= OFF_W4 && i < OFF_B4) {
+        const int o = (int)((i - OFF_W4) / NH), c = (int)((i - OFF_W4) % NH);
+        Pf[FRAG_L4 + frag_pos(1, c, o)] = v;
+        Pf[TFRAG_L4 + frag_pos(4, o, c)] = v;
     }
 }
 
-static GemmArgs gemm0() {
-    GemmArgs g{};
-    g.beta = 0.0f;
-    g.epi = EPI_NONE;
-    return g;
-}
-
-hipError_t mlp_forward(const float* P32, const uint16_t* Pb, const ClosureBufs& b, hipStream_t s) {
-    const long long offW[4] = {OFF_W1, OFF_W2, OFF_W3, OFF_W4}, offB[4] = {OFF_B1, OFF_B2, OFF_B3, OFF_B4};
-    for (int l = 0; l < 4; ++l) {
-        GemmArgs g = gemm0();
-        const long long K = l == 0 ? NFP : NH;
-        const long long N = l == 3 ? NOUT : NH;
-        g.M = b.rows; g.N = N; g.K = K;
-        g.A = l == 0 ? b.X : b.H[l - 1]; g.sam = K; g.sak = 1;
-        g.B = Pb + offW[l]; g.sbk = 1; g.sbn = K;  // B(k, n) = W[n][k]
-        g.bias = P32 + offB[l];
-        if (l < 3) {
-            g.Z = b.Z[l]; g.ldz = NH;
-            g.Cb = b.H[l]; g.ldcb = NH;
-            g.epi = EPI_GELU;
-        } else {
-            g.C = b.Y; g.ldc = NOUT;
-        }
-        hipError_t e = launch_gemm(g, s);
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
-}
-
-// dY = 2 (Y - Yt) / (rows NOUT); loss += sum (Y - Yt)^2 / (rows NOUT)
-__global__ void __launch_bounds__(256) k_mse(const float* Y, const float* Yt, long long n, float* dY,
-                                             uint16_t* dYb, double* loss) {
-    __shared__ double red[256];
+// Clears the fragment arrays (their padding stays zero) before the first fill.
+__global__ void __launch_bounds__(256) k_frag_zero(uint16_t* Pf) {
     const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-    double l = 0.0;
-    if (i < n) {
-        const float dd = Y[i] - Yt[i];
-        const float g = 2.0f * dd / (float)n;
-        dY[i] = g;
-        dYb[i] = to_bf16(g);
-        l = (double)dd * (double)dd / (double)n;
-    }
-    red[threadIdx.x] = l;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) atomicAdd(loss, red[0]);
+    if (i < NFRAG) Pf[i] = 0;
 }
 
-// db[c] = sum over rows of dZ[r][c]
-__global__ void __launch_bounds__(256) k_colsum(const float* dZ, long long rows, int cols, float* db) {
-    __shared__ float red[256];
-    const int c = blockIdx.x;
-    float acc = 0.0f;
-    for (long long r = threadIdx.x; r < rows; r += 256) acc += dZ[r * cols + c];
-    red[threadIdx.x] = acc;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) db[c] = red[0];
+// ---------------------------------------------------------------------------
+// the network, forward and backward, on tiles of rows
+// ---------------------------------------------------------------------------
+constexpr int XPITCH = NFP + 8;  // LDS row pitch of the feature block (BF16; 16-byte rows, 20 banks apart)
+constexpr int HPITCH = NH + 8;   // LDS row pitch of a hidden block
+constexpr int YPITCH = 24;       // LDS row pitch of the output gradients (16 columns)
+
+struct NetArgs {
+    const float* X;          // [.][NF] raw features
+    const float* Y;          // [.][NOUT] raw targets (training)
+    const float* st;         // standardisation
+    const uint16_t* Pf;      // weights in fragment order
+    const float* P32;        // FP32 parameters (biases)
+    long long n, rows;       // rows of X, rows of the batch
+    int draw;                // batch rows drawn from X with Philox, else row r is r
+    uint32_t k0, k1, step;
+    float* out;              // [rows][NOUT] physical outputs (forward)
+    uint16_t *Xt, *Ht[3], *dZt[3], *dYt;  // training: k_dw's operands, [rows / 16][column][16]
+    float* db;               // [row tiles][NBIAS] column sums of the pre-activation gradients
+    double* loss;
+};
+
+// Products of the wave's 32-column block for RB blocks of 32 rows: NS k steps
+// of 16, inputs from LDS, weight fragments in registers.
+template <int NS, int RB>
+__device__ __forceinline__ void mfma_cols(const uint16_t* act, int pitch, const uint4 (&w)[NS], f32x16 (&acc)[RB]) {
+    const int lane = threadIdx.x & 63, lr = lane & 31, h = lane >> 5;
+#pragma unroll
+    for (int b = 0; b < RB; ++b)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[b][r] = 0.0f;
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+#pragma unroll
+        for (int b = 0; b < RB; ++b)
+            acc[b] = mfma16(*(const uint4*)(act + (32 * b + lr) * pitch + s * 16 + 8 * h), w[s], acc[b]);
 }
 
-hipError_t mlp_backward(const uint16_t* Pb, const float* Yt, const ClosureBufs& b, float* G, double* loss,
-                        hipStream_t s) {
-    const long long R = b.rows;
-    hipLaunchKernelGGL(k_mse, dim3(nblk(R * NOUT)), dim3(256), 0, s, b.Y, Yt, R * NOUT, b.dY, b.dYb, loss);
+template <int NS>
+__device__ __forceinline__ void load_frags(const uint16_t* Pf, int ncb, int blk, uint4 (&w)[NS]) {
+    const uint4* p = (const uint4*)Pf + (threadIdx.x & 63);
+#pragma unroll
+    for (int s = 0; s < NS; ++s) w[s] = p[(s * ncb + blk) * 64];
+}
+
+// A 32-row column block (lane: column col, rows 8 q + 4 h + j in v[4 q + j])
+// as BF16 into LDS rows of `pitch` and, four rows per store, into the
+// row-blocked transpose g ([rows / 16][cols][16]) that k_dw reads.
+template <bool TR>
+__device__ __forceinline__ void put_cols(const float (&v)[16], int col, uint16_t* act, int pitch, uint16_t* g,
+                                         long long kb0, int cols) {
+    const int h = (threadIdx.x & 63) >> 5;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        uint16_t b[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            b[j] = to_bf16(v[4 * q + j]);
+            if (act) act[(8 * q + 4 * h + j) * pitch + col] = b[j];
+        }
+        if constexpr (TR) {
+            const uint2 pk = {(uint32_t)b[0] | ((uint32_t)b[1] << 16), (uint32_t)b[2] | ((uint32_t)b[3] << 16)};
+            *(uint2*)(g + ((kb0 + (q >> 1)) * cols + col) * 16 + 8 * (q & 1) + 4 * h) = pk;
+        }
+    }
+}
+
+// Sum over the tile's 32 rows of a column block, on every lane of the column.
+__device__ __forceinline__ float col_sum(const float (&v)[16]) {
+    float s = 0.0f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s += v[r];
+    return s + __shfl_xor(s, 32);
+}
+
+// One workgroup of four waves per tile of 32 RB rows; wave w owns columns
+// 32 w .. 32 w + 31 of every hidden layer, and its weight fragments of all
+// layers are loaded at the start, while the rows are gathered.  Forward: the
+// workgroup walks over tiles with its weights in registers.  The products run
+// their k steps in the order of the plain product, the hidden activations are
+// rounded to BF16 between layers and the accumulation is FP32.
+//
+// What bounds it: at the sizes of a request or a training batch (1,000 to
+// 4,096 rows, 32 to 128 workgroups) the latency of one tile's chain of four
+// (seven with the backward pass) short products.  Separate launches per layer
+// with their activations in memory took 93 us for a forward pass of 1,000
+// rows and 2.6 ms for an optimiser step of 4,096.
+template <int RB, bool TRAIN>
+__global__ void __launch_bounds__(256, RB) k_net(NetArgs a) {
+    constexpr int TR = 32 * RB;
+    static_assert(!TRAIN || RB == 1, "training tiles have 32 rows");
+    __shared__ __align__(16) uint16_t xs[TR * XPITCH];  // features, then the second hidden block
+    __shared__ __align__(16) uint16_t ha[TR * HPITCH];  // first and third hidden block
+    __shared__ __align__(16) uint16_t dys[TRAIN ? 32 * YPITCH : 8];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 31, h = lane >> 5;
+    const int col = 32 * wave + lr;
+
+    uint4 w1[NFP / 16], w2[NH / 16], w3[NH / 16], w4[NH / 16];
+    load_frags(a.Pf + FRAG_L1, 4, wave, w1);
+    load_frags(a.Pf + FRAG_L2, 4, wave, w2);
+    load_frags(a.Pf + FRAG_L3, 4, wave, w3);
+    load_frags(a.Pf + FRAG_L4, 1, 0, w4);
+    [[maybe_unused]] uint4 t4[1], t3[NH / 16], t2[NH / 16];
+    const float b1 = a.P32[OFF_B1 + col], b2 = a.P32[OFF_B2 + col], b3 = a.P32[OFF_B3 + col];
+    const int oc = lr < NOUT ? lr : 0;
+    const float b4 = a.P32[OFF_B4 + oc], ym = a.st[2 * NF + oc], ysd = a.st[2 * NF + NOUT + oc];
+    constexpr int NC = (NFP + 63) / 64;  // columns per lane of a gathered row
+    float mean[NC], inv[NC];
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+        const int c = lane + 64 * j;
+        mean[j] = c < NF ? a.st[c] : 0.0f;
+        // the binary32 reciprocal, as every kernel that standardises uses it
+        inv[j] = c < NF ? 1.0f / a.st[NF + c] : 0.0f;
+    }
+
+    for (long long tile = blockIdx.x; tile * TR < a.rows; tile += gridDim.x) {
+        const long long r0 = tile * TR;
+        // source row of tile row `lane % TR`
+        long long src = r0 + (lane & (TR - 1));
+        const bool in = src < a.rows;
+        if (TRAIN && a.draw) {
+            const U4 w = rng_block(Key{a.k0, a.k1}, (uint32_t)src, a.step, 0u, P_MLP_BATCH, 0u);
+            const uint64_t v = ((uint64_t)w.y << 32) | w.x;
+            src = (long long)(v % (uint64_t)a.n);
+        }
+        if (!in) src = -1;
+        // standardised features of the wave's rows (zero past the batch)
+#pragma unroll 1
+        for (int g = 0; g < RB; ++g) {
+            float x[8][NC];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const long long sr = __shfl(src, (g * 4 + wave) * 8 + i);
+#pragma unroll
+                for (int j = 0; j < NC; ++j) {
+                    const int c = lane + 64 * j;
+                    x[i][j] = (sr >= 0 && c < NF) ? a.X[sr * NF + c] : mean[j];
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+#pragma unroll
+                for (int j = 0; j < NC; ++j) {
+                    const int c = lane + 64 * j;
+                    if (c < NFP) xs[((g * 4 + wave) * 8 + i) * XPITCH + c] = to_bf16((x[i][j] - mean[j]) * inv[j]);
+                }
+        }
+        // the targets (training), or the LB velocities the outputs are
+        // relative to, of the rows this wave finishes, in flight until then
+        float uc[16];
+        [[maybe_unused]] float yt[16];
+        if (wave < RB) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const long long sr = __shfl(src, 32 * wave + 8 * (r >> 2) + 4 * h + (r & 3));
+                uc[r] = (sr >= 0 && lr < 3) ? a.X[sr * NF + UC + lr] : 0.0f;
+                if constexpr (TRAIN) yt[r] = (sr >= 0 && lr < NOUT) ? a.Y[sr * NOUT + lr] : 0.0f;
+            }
+        }
+        __syncthreads();
+        const long long kb0 = 2 * tile;
+        if constexpr (TRAIN) {
+            for (int c = threadIdx.x; c < NFP; c += 256)
+#pragma unroll
+                for (int b = 0; b < 2; ++b) {
+                    uint32_t pk[8];
+#pragma unroll
+                    for (int i = 0; i < 8; ++i)
+                        pk[i] = (uint32_t)xs[(16 * b + 2 * i) * XPITCH + c] |
+                                ((uint32_t)xs[(16 * b + 2 * i + 1) * XPITCH + c] << 16);
+                    uint4* o = (uint4*)(a.Xt + ((kb0 + b) * NFP + c) * 16);
+                    o[0] = uint4{pk[0], pk[1], pk[2], pk[3]};
+                    o[1] = uint4{pk[4], pk[5], pk[6], pk[7]};
+                }
+        }
+        f32x16 acc[RB];
+        float z1[16], z2[16], z3[16], v[16];
+        auto hidden = [&](float bias, float (&z)[16], uint16_t* act, uint16_t* g) {
+#pragma unroll
+            for (int b = 0; b < RB; ++b) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    z[r] = acc[b][r] + bias;
+                    v[r] = gelu(z[r]);
+                }
+                put_cols<TRAIN>(v, col, act + 32 * b * HPITCH, HPITCH, g, kb0, NH);
+            }
+        };
+        mfma_cols<NFP / 16, RB>(xs, XPITCH, w1, acc);
+        if constexpr (TRAIN) {
+            // the backward pass's weights take the place of the first layer's
+            load_frags(a.Pf + TFRAG_L4, 4, wave, t4);
+            load_frags(a.Pf + TFRAG_L3, 4, wave, t3);
+            load_frags(a.Pf + TFRAG_L2, 4, wave, t2);
+        }
+        hidden(b1, z1, ha, a.Ht[0]);
+        __syncthreads();
+        mfma_cols<NH / 16, RB>(ha, HPITCH, w2, acc);
+        hidden(b2, z2, xs, a.Ht[1]);
+        __syncthreads();
+        mfma_cols<NH / 16, RB>(xs, HPITCH, w3, acc);
+        hidden(b3, z3, ha, a.Ht[2]);
+        __syncthreads();
+        if (wave < RB) {
+            f32x16 y[1];
+            mfma_cols<NH / 16, 1>(ha + 32 * wave * HPITCH, HPITCH, w4, y);
+            if constexpr (!TRAIN) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const long long row = r0 + 32 * wave + 8 * (r >> 2) + 4 * h + (r & 3);
+                    if (lr < NOUT && row < a.rows) a.out[row * NOUT + lr] = (y[0][r] + b4) * ysd + ym + uc[r];
+                }
+            } else {
+                const float nn = (float)(a.rows * NOUT);
+                double l = 0.0;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const bool ok = lr < NOUT && r0 + 8 * (r >> 2) + 4 * h + (r & 3) < a.rows;
+                    const float dd = ok ? (y[0][r] + b4) - ((yt[r] - uc[r]) - ym) / ysd : 0.0f;
+                    v[r] = 2.0f * dd / nn;
+                    l += (double)dd * (double)dd / (double)(a.rows * NOUT);
+                }
+                if (lr < 16) put_cols<true>(v, lr, dys, YPITCH, a.dYt, kb0, 16);
+                const float s = col_sum(v);
+                if (lane < NOUT) a.db[tile * NBIAS + 3 * NH + lane] = s;
+#pragma unroll
+                for (int o = 32; o > 0; o >>= 1) l += __shfl_xor(l, o);
+                if (lane == 0) atomicAdd(a.loss, l);
+            }
+        }
+        if constexpr (TRAIN) {
+            __syncthreads();
+            auto back = [&](const float (&z)[16], uint16_t* act, uint16_t* g, int layer) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) v[r] = acc[0][r] * gelu_grad(z[r]);
+                put_cols<true>(v, col, act, HPITCH, g, kb0, NH);
+                const float s = col_sum(v);
+                if (h == 0) a.db[tile * NBIAS + layer * NH + col] = s;
+            };
+            mfma_cols<1, 1>(dys, YPITCH, t4, acc);
+            back(z3, ha, a.dZt[2], 2);
+            __syncthreads();
+            mfma_cols<NH / 16, 1>(ha, HPITCH, t3, acc);
+            back(z2, xs, a.dZt[1], 1);
+            __syncthreads();
+            mfma_cols<NH / 16, 1>(xs, HPITCH, t2, acc);
+            back(z1, nullptr, a.dZt[0], 0);
+            break;  // one tile per workgroup
+        }
+    }
+}
+
+// Rows of physical outputs.  Tiles of 32 rows spread a small batch over more
+// of the chip; from 8,192 rows (256 such tiles) on, 64-row tiles read each
+// weight fragment's operands once per two products.  Two workgroups per CU
+// walk over what is left.
+hipError_t net_forward(const float* X, long long rows, const float* st, const uint16_t* Pf, const float* P32, float* out,
+                       hipStream_t s) {
+    NetArgs a{};
+    a.X = X; a.st = st; a.Pf = Pf; a.P32 = P32; a.n = rows; a.rows = rows; a.out = out;
+    const long long most = 512;
+    if (rows <= 8192) {
+        hipLaunchKernelGGL((k_net<1, false>), dim3((unsigned)((rows + 31) / 32)), dim3(256), 0, s, a);
+    } else {
+        const long long tiles = (rows + 63) / 64;
+        hipLaunchKernelGGL((k_net<2, false>), dim3((unsigned)(tiles < most ? tiles : most)), dim3(256), 0, s, a);
+    }
+    return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------
+// training
+// ---------------------------------------------------------------------------
+// Weight gradients dW[o][i] = sum over rows of dZ[row][o] In[row][i].  The
+// operands lie in blocks of 16 rows, [rows / 16][column][16], so that a k
+// step's fragment of 32 columns is one contiguous KiB, read straight into
+// registers.  Workgroup (j, s) takes input block j of one layer (waves: the
+// four output blocks) over split s of the rows and writes its own partial, so
+// that the 18 x S workgroups fill the chip and no order depends on atomics;
+// job 18 sums the bias gradients of the split's tiles.  With one split per
+// 128 rows (at most 64 splits) a batch of 4,096 has 608 workgroups; as one
+// product per layer over all rows it had 10, and took 0.64 ms.
+struct DwArgs {
+    const uint16_t *Xt, *Ht[3], *dZt[3], *dYt;
+    const float* db;
+    float* part;             // [S][NPARAM]
+    long long nkb, chunk;    // 16-row blocks in all, per split
+};
+
+__global__ void __launch_bounds__(256) k_dw(DwArgs a) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 31, h = lane >> 5;
+    const int j = blockIdx.x;
+    const long long kb0 = blockIdx.y * a.chunk;
+    const long long kb1 = kb0 + a.chunk < a.nkb ? kb0 + a.chunk : a.nkb;
+    float* part = a.part + blockIdx.y * NPARAM;
+    if (j == 18) {
+        // chunk is even and nkb is even: a tile of 32 rows is two blocks
+        for (int c = threadIdx.x; c < NBIAS; c += 256) {
+            float s = 0.0f;
+            for (long long t = kb0 / 2; t < kb1 / 2; ++t) s += a.db[t * NBIAS + c];
+            const long long o = c < NH ? OFF_B1 + c
+                                       : (c < 2 * NH ? OFF_B2 + c - NH : (c < 3 * NH ? OFF_B3 + c - 2 * NH : OFF_B4 + c - 3 * NH));
+            part[o] = s;
+        }
+        return;
+    }
+    const uint16_t *A, *B;
+    int ca = NH, cb = NH, ib, ob = wave, om = NH;
+    long long off;
+    if (j < 9) { A = a.dZt[0]; B = a.Xt; cb = NFP; ib = j; off = OFF_W1; }
+    else if (j < 13) { A = a.dZt[1]; B = a.Ht[0]; ib = j - 9; off = OFF_W2; }
+    else if (j < 17) { A = a.dZt[2]; B = a.Ht[1]; ib = j - 13; off = OFF_W3; }
+    else { A = a.dYt; B = a.Ht[2]; ca = 16; ib = wave; ob = 0; om = NOUT; off = OFF_W4; }
+    const int ac = 32 * ob + lr;
+    const uint16_t* pa = A + (kb0 * ca + (ac < ca ? ac : 0)) * 16 + 8 * h;
+    const uint16_t* pb = B + (kb0 * cb + 32 * ib + lr) * 16 + 8 * h;
+    const bool az = ac >= ca;
+    f32x16 acc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+#pragma unroll 4
+    for (long long kb = kb0; kb < kb1; ++kb) {
+        uint4 x = *(const uint4*)pa;
+        const uint4 y = *(const uint4*)pb;
+        if (az) x = uint4{0u, 0u, 0u, 0u};
+        acc = mfma16(x, y, acc);
+        pa += ca * 16;
+        pb += cb * 16;
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int m = 32 * ob + 8 * (r >> 2) + 4 * h + (r & 3);
+        if (m < om) part[off + (long long)m * cb + 32 * ib + lr] = acc[r];
+    }
+}
+
+// The gradient as the sum of the splits, in their order; with ADAM it goes
+// through Adam (Kingma & Ba) on the FP32 parameters, with the bias-corrected
+// moment estimates, and the BF16 copies follow; else it is written to G.
+struct ReduceArgs {
+    const float* part;
+    int S;
+    float *G, *P, *m, *v;
+    uint16_t* Pf;
+    float lr, b1, b2, eps, c1, c2;
+};
+
+template <bool ADAM>
+__global__ void __launch_bounds__(256) k_reduce(ReduceArgs a) {
+    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
+    if (i >= NPARAM) return;
+    float g = 0.0f;
+#pragma unroll 8
+    for (int s = 0; s < a.S; ++s) g += a.part[s * NPARAM + i];
+    if constexpr (!ADAM) {
+        a.G[i] = g;
+    } else {
+        const float mi = a.b1 * a.m[i] + (1.0f - a.b1) * g;
+        const float vi = a.b2 * a.v[i] + (1.0f - a.b2) * g * g;
+        a.m[i] = mi;
+        a.v[i] = vi;
+        const float p = a.P[i] - a.lr * (mi / a.c1) / (sqrtf(vi / a.c2) + a.eps);
+        a.P[i] = p;
+        frag_store(a.Pf, i, to_bf16(p));
+    }
+}
+
+// Carve-up of the training scratch for a batch.
+struct TrainBufs {
+    uint16_t *Xt, *Ht[3], *dZt[3], *dYt;
+    float *db, *part;
+    long long nkb, chunk;
+    int S;
+};
+
+static size_t train_carve(unsigned char* base, long long rows, TrainBufs& b) {
+    size_t o = 0;
+    auto take = [&](size_t bytes) { unsigned char* p = base + o; o += (bytes + 255) & ~(size_t)255; return p; };
+    const long long tiles = (rows + 31) / 32;
+    b.nkb = 2 * tiles;
+    b.chunk = 8;
+    while ((b.nkb + b.chunk - 1) / b.chunk > 64) b.chunk += 2;
+    b.S = (int)((b.nkb + b.chunk - 1) / b.chunk);
+    b.Xt = (uint16_t*)take((size_t)b.nkb * NFP * 32);
+    for (int l = 0; l < 3; ++l) {
+        b.Ht[l] = (uint16_t*)take((size_t)b.nkb * NH * 32);
+        b.dZt[l] = (uint16_t*)take((size_t)b.nkb * NH * 32);
+    }
+    b.dYt = (uint16_t*)take((size_t)b.nkb * 16 * 32);
+    b.db = (float*)take((size_t)tiles * NBIAS * 4);
+    b.part = (float*)take((size_t)b.S * NPARAM * 4);
+    return o;
+}
+
+size_t train_bytes(long long rows) {
+    TrainBufs b;
+    return train_carve(nullptr, rows, b);
+}
+
+hipError_t net_gradient(const NetBatch& q, void* scratch, float* G, const AdamState* adam, double* loss, hipStream_t s) {
+    TrainBufs b;
+    train_carve((unsigned char*)scratch, q.rows, b);
+    NetArgs a{};
+    a.X = q.X; a.Y = q.Y; a.st = q.st; a.Pf = q.Pf; a.P32 = q.P32; a.n = q.n; a.rows = q.rows; a.draw = q.draw ? 1 : 0;
+    a.k0 = q.k0; a.k1 = q.k1; a.step = q.step; a.Xt = b.Xt; a.dYt = b.dYt; a.db = b.db; a.loss = loss;
+    DwArgs d{};
+    d.Xt = b.Xt; d.dYt = b.dYt; d.db = b.db; d.part = b.part; d.nkb = b.nkb; d.chunk = b.chunk;
+    for (int l = 0; l < 3; ++l) {
+        d.Ht[l] = a.Ht[l] = b.Ht[l];
+        d.dZt[l] = a.dZt[l] = b.dZt[l];
+    }
+    hipLaunchKernelGGL((k_net<1, true>), dim3((unsigned)(b.nkb / 2)), dim3(256), 0, s, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const long long offW[4] = {OFF_W1, OFF_W2, OFF_W3, OFF_W4}, offB[4] = {OFF_B1, OFF_B2, OFF_B3, OFF_B4};
-    for (int l = 3; l >= 0; --l) {
-        const long long K = l == 0 ? NFP : NH;      // inputs of layer l
-        const long long N = l == 3 ? NOUT : NH;     // outputs of layer l
-        const float* dZ = l == 3 ? b.dY : b.dZ[l];
-        const uint16_t* dZb = l == 3 ? b.dYb : b.dZb[l];
-        const uint16_t* In = l == 0 ? b.X : b.H[l - 1];
-        // weight gradient dW[o][i] = sum_r dZ[r][o] In[r][i]
-        GemmArgs g = gemm0();
-        g.M = N; g.N = K; g.K = R;
-        g.A = dZb; g.sam = 1; g.sak = N;
-        g.B = In; g.sbk = K; g.sbn = 1;
-        g.C = G + offW[l]; g.ldc = K;
-        if ((e = launch_gemm(g, s)) != hipSuccess) return e;
-        hipLaunchKernelGGL(k_colsum, dim3((unsigned)N), dim3(256), 0, s, dZ, R, (int)N, G + offB[l]);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        if (l == 0) break;
-        // input gradient, times GELU' of the previous pre-activation
-        GemmArgs h = gemm0();
-        h.M = R; h.N = K; h.K = N;
-        h.A = dZb; h.sam = N; h.sak = 1;
-        h.B = Pb + offW[l]; h.sbk = K; h.sbn = 1;  // B(k = o, n = i) = W[o][i]
-        h.epi = EPI_GELU_GRAD; h.Zprev = b.Z[l - 1]; h.ldzp = NH;
-        h.C = b.dZ[l - 1]; h.ldc = NH;
-        h.Cb = b.dZb[l - 1]; h.ldcb = NH;
-        if ((e = launch_gemm(h, s)) != hipSuccess) return e;
+    hipLaunchKernelGGL(k_dw, dim3(19, (unsigned)b.S), dim3(256), 0, s, d);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    ReduceArgs r{};
+    r.part = b.part; r.S = b.S; r.G = G;
+    if (!adam) {
+        hipLaunchKernelGGL(k_reduce<false>, dim3(nblk(NPARAM)), dim3(256), 0, s, r);
+        return hipGetLastError();
     }
-    return hipSuccess;
-}
-
-// Adam (Kingma & Ba) on the FP32 parameters, with the bias-corrected moment
-// estimates; the BF16 copy follows.
-__global__ void __launch_bounds__(256) k_adam(float* P, uint16_t* Pb, const float* G, float* m, float* v,
-                                              long long n, float lr, float b1, float b2, float eps, float c1,
-                                              float c2) {
-    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    const float g = G[i];
-    const float mi = b1 * m[i] + (1.0f - b1) * g;
-    const float vi = b2 * v[i] + (1.0f - b2) * g * g;
-    m[i] = mi;
-    v[i] = vi;
-    const float p = P[i] - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
-    P[i] = p;
-    Pb[i] = to_bf16(p);
-}
-
-hipError_t mlp_adam(float* P32, uint16_t* Pb, const float* G, float* m, float* v, long long t, float lr,
-                    float beta1, float beta2, float eps, hipStream_t s) {
-    const float c1 = 1.0f - powf(beta1, (float)t), c2 = 1.0f - powf(beta2, (float)t);
-    hipLaunchKernelGGL(k_adam, dim3(nblk(NPARAM)), dim3(256), 0, s, P32, Pb, G, m, v, NPARAM, lr, beta1, beta2,
-                       eps, c1, c2);
+    r.P = adam->P32; r.Pf = adam->Pf; r.m = adam->m; r.v = adam->v;
+    r.lr = adam->lr; r.b1 = adam->beta1; r.b2 = adam->beta2; r.eps = adam->eps;
+    r.c1 = 1.0f - powf(adam->beta1, (float)adam->t);
+    r.c2 = 1.0f - powf(adam->beta2, (float)adam->t);
+    hipLaunchKernelGGL(k_reduce<true>, dim3(nblk(NPARAM)), dim3(256), 0, s, r);
     return hipGetLastError();
 }
 
 // Uniform(-a, a) weights with a = sqrt(6 / (fan_in + fan_out)) over the real
 // inputs (Glorot), zero biases, zero padding columns, zero Adam moments.
-__global__ void __launch_bounds__(256) k_mlp_init(float* P, uint16_t* Pb, float* m, float* v, uint32_t k0,
+__global__ void __launch_bounds__(256) k_mlp_init(float* P, uint16_t* Pf, float* m, float* v, uint32_t k0,
                                                   uint32_t k1) {
     const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
     if (i >= NPARAM) return;
@@ -282,13 +578,25 @@ __global__ void __launch_bounds__(256) k_mlp_init(float* P, uint16_t* Pb, float*
         w = (float)((2.0 * u01(r.x, r.y) - 1.0) * a);
     }
     P[i] = w;
-    Pb[i] = to_bf16(w);
+    frag_store(Pf, i, to_bf16(w));
     m[i] = 0.0f;
     v[i] = 0.0f;
 }
 
-hipError_t mlp_init(float* P32, uint16_t* Pb, float* m, float* v, uint32_t k0, uint32_t k1, hipStream_t s) {
-    hipLaunchKernelGGL(k_mlp_init, dim3(nblk(NPARAM)), dim3(256), 0, s, P32, Pb, m, v, k0, k1);
+hipError_t mlp_init(float* P32, uint16_t* Pf, float* m, float* v, uint32_t k0, uint32_t k1, hipStream_t s) {
+    hipLaunchKernelGGL(k_frag_zero, dim3(nblk(NFRAG)), dim3(256), 0, s, Pf);
+    hipLaunchKernelGGL(k_mlp_init, dim3(nblk(NPARAM)), dim3(256), 0, s, P32, Pf, m, v, k0, k1);
+    return hipGetLastError();
+}
+
+__global__ void __launch_bounds__(256) k_frag_fill(const float* P, uint16_t* Pf) {
+    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
+    if (i < NPARAM) frag_store(Pf, i, to_bf16(P[i]));
+}
+
+hipError_t mlp_refresh(const float* P32, uint16_t* Pf, hipStream_t s) {
+    hipLaunchKernelGGL(k_frag_zero, dim3(nblk(NFRAG)), dim3(256), 0, s, Pf);
+    hipLaunchKernelGGL(k_frag_fill, dim3(nblk(NPARAM)), dim3(256), 0, s, P32, Pf);
     return hipGetLastError();
 }
 
@@ -354,67 +662,6 @@ hipError_t mlp_stats(const float* X, const float* Y, long long n, double* sums, 
     hipLaunchKernelGGL(k_colstats, dim3(gx, (NF + 255) / 256), dim3(256), 0, s, X, n, NF, rows_per, sums);
     hipLaunchKernelGGL(k_colstats_y, dim3(gx, 1), dim3(64), 0, s, Y, X, n, rows_per, sums + 2 * NF);
     hipLaunchKernelGGL(k_stats_final, dim3(2), dim3(256), 0, s, sums, sums + 2 * NF, n, stats);
-    return hipGetLastError();
-}
-
-// Row r of the batch: source row idx (drawn uniformly from n with Philox when
-// `draw`, else r), standardised; features to BF16 with zero padding.  Every
-// kernel standardises a feature as (x - mean) times the binary32 reciprocal of
-// its standard deviation, so that training and the fused inference see the
-// same values (the fused kernel reads the reciprocals from LDS, a multiply per
-// feature where a division took 6 % of its time).
-__global__ void __launch_bounds__(256) k_gather(const float* X, const float* Y, long long n, const float* st,
-                                                long long rows, int draw, uint32_t k0, uint32_t k1,
-                                                uint32_t step, uint16_t* Xb, float* Yb) {
-    const long long r = blockIdx.x;
-    if (r >= rows) return;
-    long long src = r;
-    if (draw) {
-        const U4 w = rng_block(Key{k0, k1}, (uint32_t)r, step, 0u, P_MLP_BATCH, 0u);
-        const uint64_t v = ((uint64_t)w.y << 32) | w.x;
-        src = (long long)(v % (uint64_t)n);
-    }
-    for (int c = threadIdx.x; c < NFP; c += 256) {
-        float x = 0.0f;
-        if (c < NF) x = (X[src * NF + c] - st[c]) * (1.0f / st[NF + c]);
-        Xb[r * NFP + c] = to_bf16(x);
-    }
-    if (Y && threadIdx.x < NOUT) {
-        const int c = threadIdx.x;
-        const float y = Y[src * NOUT + c] - (c < 3 ? X[src * NF + UC + c] : 0.0f);
-        Yb[r * NOUT + c] = (y - st[2 * NF + c]) / st[2 * NF + NOUT + c];
-    }
-}
-
-hipError_t mlp_gather(const float* X, const float* Y, long long n, const float* stats, long long rows, bool draw,
-                      uint32_t k0, uint32_t k1, uint32_t step, uint16_t* Xb, float* Yb, hipStream_t s) {
-    hipLaunchKernelGGL(k_gather, dim3((unsigned)rows), dim3(256), 0, s, X, Y, n, stats, rows, draw ? 1 : 0, k0, k1,
-                       step, Xb, Yb);
-    return hipGetLastError();
-}
-
-__global__ void __launch_bounds__(256) k_refresh_bf16(const float* P, uint16_t* Pb, long long n) {
-    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (i < n) Pb[i] = to_bf16(P[i]);
-}
-
-hipError_t mlp_refresh_bf16(const float* P32, uint16_t* Pb, hipStream_t s) {
-    hipLaunchKernelGGL(k_refresh_bf16, dim3(nblk(NPARAM)), dim3(256), 0, s, P32, Pb, NPARAM);
-    return hipGetLastError();
-}
-
-__global__ void __launch_bounds__(256) k_destd(const float* Y, const float* st, const float* X, long long n,
-                                               float* out) {
-    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    const int c = (int)(i % NOUT);
-    const long long r = i / NOUT;
-    out[i] = Y[i] * st[2 * NF + NOUT + c] + st[2 * NF + c] + (c < 3 ? X[r * NF + UC + c] : 0.0f);
-}
-
-hipError_t mlp_destandardize(const float* Y, const float* stats, const float* X, long long rows, float* out,
-                             hipStream_t s) {
-    hipLaunchKernelGGL(k_destd, dim3(nblk(rows * NOUT)), dim3(256), 0, s, Y, stats, X, rows * NOUT, out);
     return hipGetLastError();
 }
 
@@ -541,8 +788,6 @@ hipError_t closure_to_acc(const InstDesc* D, int inst, long long nslab, const fl
 // ---------------------------------------------------------------------------
 // fused inference: features and the four layers in one kernel
 // ---------------------------------------------------------------------------
-constexpr int BMS = 12;  // floats per band node: 10 moments, shear rate, pad
-
 // The 10 moments and the shear rate of every node of the rows [y0, y0 + nyb)
 // that the slab's 3x3x3 stencils reach, computed exactly as the per-node
 // feature kernel computes them.
@@ -580,26 +825,6 @@ __global__ void __launch_bounds__(256) k_band_moments(const InstDesc* __restrict
 // network output Y and the centre node's LB velocity uc.
 constexpr int FNT = 256;       // threads per workgroup: four waves
 constexpr int FR = 32 * (FNT / 64);  // rows per workgroup, 32 per wave
-constexpr int XPITCH = NFP + 8;  // LDS row pitch of the feature block (BF16 elements, 16-byte rows)
-constexpr int HPITCH = NH + 8;   // LDS row pitch of a hidden block
-
-// Weights of one layer in fragment order (see FRAG_L1): one thread per value.
-__global__ void __launch_bounds__(256) k_frag_weights(const uint16_t* __restrict__ Pb, uint16_t* Pf) {
-    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (i >= NFRAG) return;
-    long long base, off;
-    int K, ncb, nvalid;
-    if (i < FRAG_L2) { base = FRAG_L1; off = OFF_W1; K = NFP; ncb = 4; nvalid = NH; }
-    else if (i < FRAG_L3) { base = FRAG_L2; off = OFF_W2; K = NH; ncb = 4; nvalid = NH; }
-    else if (i < FRAG_L4) { base = FRAG_L3; off = OFF_W3; K = NH; ncb = 4; nvalid = NH; }
-    else { base = FRAG_L4; off = OFF_W4; K = NH; ncb = 1; nvalid = NOUT; }
-    const long long e = i - base;
-    const int j = (int)(e & 7), t = (int)((e >> 3) & 63);
-    const long long sb = e >> 9;  // step * ncb + block
-    const int b = (int)(sb % ncb), st = (int)(sb / ncb);
-    const int n = 32 * b + (t & 31), k = 16 * st + 8 * (t >> 5) + j;
-    Pf[i] = n < nvalid ? Pb[off + (long long)n * K + k] : (uint16_t)0;
-}
 
 // One layer for the wave's 32 rows: each k step of 16 loads the rows' inputs
 // from LDS and every column block's weight fragment (one coalesced 1 KiB
@@ -724,9 +949,8 @@ __global__ void __launch_bounds__(FNT) k_mlp_fused(const InstDesc* __restrict__ 
 }
 
 hipError_t closure_predict(int lb_fp, const InstDesc* D, int inst, long long nslab, long long nband, int y0,
-                           int nyb, const void* f, float* M, const float* stats, const uint16_t* Pb,
-                           uint16_t* Pf, const float* P32, float* Y, float* uc, hipStream_t s) {
-    hipLaunchKernelGGL(k_frag_weights, dim3(nblk(NFRAG)), dim3(256), 0, s, Pb, Pf);
+                           int nyb, const void* f, float* M, const float* stats, const uint16_t* Pf,
+                           const float* P32, float* Y, float* uc, hipStream_t s) {
     if (lb_fp == 64)
         hipLaunchKernelGGL(k_band_moments<double>, dim3(nblk(nband)), dim3(256), 0, s, D, inst, (const double*)f,
                            y0, nyb, M);

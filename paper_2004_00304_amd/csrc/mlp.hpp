@@ -24,16 +24,22 @@ constexpr long long OFF_B3 = OFF_W3 + (long long)NH * NH;
 constexpr long long OFF_W4 = OFF_B3 + NH;
 constexpr long long OFF_B4 = OFF_W4 + (long long)NOUT * NH;
 constexpr long long NPARAM = OFF_B4 + NOUT;
-// The BF16 weights in the order the fused inference kernel reads them: for
-// layer l, k step s (16 inputs), 32-column block b and lane t of a wave, the
-// 8 values W[32 b + t % 32][16 s + 8 (t / 32) + j], j = 0..7 (zero past the
-// last output), so that every lane's 16 bytes of a (step, block) are
-// contiguous.
+constexpr int NBIAS = 3 * NH + NOUT;
+// The BF16 weights in the order the matrix cores read them as the B operand of
+// a product: for layer l, k step s (16 inputs), 32-column block b and lane t of
+// a wave, the 8 values W[32 b + t % 32][16 s + 8 (t / 32) + j], j = 0..7 (zero
+// past the last output), so that every lane's 16 bytes of a (step, block) are
+// contiguous.  TFRAG: the transposes of layers 2 to 4, the B operand of the
+// input gradients (k runs over the layer's outputs, 9 padded to 16 in the
+// last).
 constexpr long long FRAG_L1 = 0;
 constexpr long long FRAG_L2 = FRAG_L1 + (long long)(NFP / 16) * 4 * 512;
 constexpr long long FRAG_L3 = FRAG_L2 + (long long)(NH / 16) * 4 * 512;
 constexpr long long FRAG_L4 = FRAG_L3 + (long long)(NH / 16) * 4 * 512;
-constexpr long long NFRAG = FRAG_L4 + (long long)(NH / 16) * 1 * 512;
+constexpr long long TFRAG_L2 = FRAG_L4 + (long long)(NH / 16) * 1 * 512;
+constexpr long long TFRAG_L3 = TFRAG_L2 + (long long)(NH / 16) * 4 * 512;
+constexpr long long TFRAG_L4 = TFRAG_L3 + (long long)(NH / 16) * 4 * 512;
+constexpr long long NFRAG = TFRAG_L4 + 4 * 512;
 // Standardisation: feature mean[NF], std[NF], target mean[NOUT], std[NOUT].
 constexpr long long NSTATS = 2 * NF + 2 * NOUT;
 // The network's velocity outputs are relative to the LB velocity of the node
@@ -41,67 +47,54 @@ constexpr long long NSTATS = 2 * NF + 2 * NOUT;
 // stencil, features UC..UC+2.  Targets and forward outputs in physical units
 // are absolute.
 constexpr int UC = 13 * 10 + 1;
+constexpr int BMS = 12;  // floats per band node of the fused inference: 10 moments, shear rate, pad
 
-enum GemmEpilogue { EPI_NONE = 0, EPI_GELU = 1, EPI_GELU_GRAD = 2 };
-
-// C(m, n) = beta * C(m, n) + sum_k A(m, k) B(k, n) (+ bias[n]), BF16 operands
-// A(m, k) = A[m * sam + k * sak], B(k, n) = B[k * sbk + n * sbn], FP32
-// accumulation.  Outputs (any may be null): Z = value before the activation,
-// C = value after it (FP32), Cb = the same rounded to BF16.
+// C[M][N] = A[M][K] B[N][K]^T, row-major BF16 operands, FP32 accumulation and result.
 struct GemmArgs {
     long long M, N, K;
-    const uint16_t* A; long long sam, sak;
-    const uint16_t* B; long long sbk, sbn;
-    const float* bias;
-    float* C; long long ldc; float beta;
-    uint16_t* Cb; long long ldcb;
-    float* Z; long long ldz;
-    const float* Zprev; long long ldzp;  // EPI_GELU_GRAD: multiply by GELU'(Zprev)
-    int epi;
+    const uint16_t* A;
+    const uint16_t* B;
+    float* C;
 };
 
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s);
 
-// Activations of a batch of rows: inputs, pre-activations and BF16 outputs of
-// the hidden layers, the network output, and the gradients of back-propagation.
-struct ClosureBufs {
-    long long rows;
-    uint16_t* X;              // [rows][NFP] standardised features (BF16)
-    float* Z[3];              // [rows][NH] hidden pre-activations
-    uint16_t* H[3];           // [rows][NH] hidden activations (BF16)
-    float* Y;                 // [rows][NOUT] output (standardised units)
-    float* dY; uint16_t* dYb; // [rows][NOUT] loss gradient
-    float* dZ[3]; uint16_t* dZb[3];  // [rows][NH] hidden pre-activation gradients
+// Network on rows of raw features [rows][NF]: physical outputs [rows][NOUT].
+// st: standardisation, Pf: BF16 weights in fragment order, P32: FP32
+// parameters (biases).
+hipError_t net_forward(const float* X, long long rows, const float* st, const uint16_t* Pf, const float* P32, float* out,
+                       hipStream_t s);
+
+// One batch of raw features and targets: `rows` rows, drawn uniformly from
+// the n rows of X, Y with Philox when `draw`, else the first ones.
+struct NetBatch {
+    const float *X, *Y, *st;
+    const uint16_t* Pf;
+    const float* P32;
+    long long n, rows;
+    bool draw;
+    uint32_t k0, k1, step;
 };
-// Bytes of ClosureBufs for `rows` rows, and the carve-up of such an area
-// (every buffer starts on a 256-byte boundary).
-constexpr size_t closure_al256(size_t b) { return (b + 255) & ~(size_t)255; }
-constexpr size_t closure_fwd_bytes(long long rows) {
-    return closure_al256((size_t)rows * NFP * 2) +
-           3 * (closure_al256((size_t)rows * NH * 4) + closure_al256((size_t)rows * NH * 2)) +
-           closure_al256((size_t)rows * NOUT * 4);
-}
-size_t closure_bufs_bytes(long long rows, bool backward);
-void closure_bufs_carve(unsigned char* base, long long rows, bool backward, ClosureBufs& b);
-
-// Network passes.  P32: FP32 parameters, Pb: their BF16 copy.
-hipError_t mlp_forward(const float* P32, const uint16_t* Pb, const ClosureBufs& b, hipStream_t s);
+// Adam's state and the step number t >= 1 of the update.
+struct AdamState {
+    float *P32, *m, *v;
+    uint16_t* Pf;
+    long long t;
+    float lr, beta1, beta2, eps;
+};
+// Scratch bytes of a batch of `rows` rows.
+size_t train_bytes(long long rows);
 // Loss (mean squared error over rows x NOUT, accumulated into *loss) and the
-// parameter gradient G (FP32, layout of the parameter block) of one batch.
-hipError_t mlp_backward(const uint16_t* Pb, const float* Yt, const ClosureBufs& b, float* G, double* loss,
-                        hipStream_t s);
-hipError_t mlp_adam(float* P32, uint16_t* Pb, const float* G, float* m, float* v, long long t, float lr,
-                    float beta1, float beta2, float eps, hipStream_t s);
-hipError_t mlp_init(float* P32, uint16_t* Pb, float* m, float* v, uint32_t k0, uint32_t k1, hipStream_t s);
-hipError_t mlp_refresh_bf16(const float* P32, uint16_t* Pb, hipStream_t s);
-// Output rows in standardised units -> physical units.
-hipError_t mlp_destandardize(const float* Y, const float* stats, const float* X, long long rows, float* out,
-                             hipStream_t s);
+// parameter gradient of a batch: into G (layout of the parameter block), or
+// with `adam` straight through an Adam step.
+hipError_t net_gradient(const NetBatch& q, void* scratch, float* G, const AdamState* adam, double* loss, hipStream_t s);
 
-// Data: column statistics of raw features / targets, standardised batches.
+hipError_t mlp_init(float* P32, uint16_t* Pf, float* m, float* v, uint32_t k0, uint32_t k1, hipStream_t s);
+// The fragment arrays from the FP32 parameters.
+hipError_t mlp_refresh(const float* P32, uint16_t* Pf, hipStream_t s);
+
+// Column statistics of raw features / targets.
 hipError_t mlp_stats(const float* X, const float* Y, long long n, double* sums, float* stats, hipStream_t s);
-hipError_t mlp_gather(const float* X, const float* Y, long long n, const float* stats, long long rows,
-                      bool draw, uint32_t k0, uint32_t k1, uint32_t step, uint16_t* Xb, float* Yb, hipStream_t s);
 
 // Coupling: features of the slab nodes of one channel from its populations,
 // either raw into an FP64 accumulator (facc, [nslab][NF]) or standardised
@@ -114,12 +107,11 @@ hipError_t closure_to_acc(const InstDesc* D, int inst, long long nslab, const fl
                           const float* uc, double* acc, double* prof, int do_prof, hipStream_t s);
 // Fused inference of every slab node of the current populations: the moments
 // and shear rate of the band rows [y0, y0 + nyb) into M (nband x 12 floats),
-// then features and the four layers in one kernel (Pf: scratch for the
-// weights in fragment order, NFRAG BF16 values).  Y: standardised output
+// then features and the four layers in one kernel.  Y: standardised output
 // [nslab][NOUT]; uc: the node's LB velocity [nslab][3].
 hipError_t closure_predict(int lb_fp, const InstDesc* D, int inst, long long nslab, long long nband, int y0,
-                           int nyb, const void* f, float* M, const float* stats, const uint16_t* Pb,
-                           uint16_t* Pf, const float* P32, float* Y, float* uc, hipStream_t s);
+                           int nyb, const void* f, float* M, const float* stats, const uint16_t* Pf,
+                           const float* P32, float* Y, float* uc, hipStream_t s);
 // Physical units from a standardised output and the nodes' LB velocities.
 hipError_t mlp_destandardize_uc(const float* Y, const float* stats, const float* uc, long long rows, float* out,
                                 hipStream_t s);

@@ -492,8 +492,8 @@ class Sim:
 
     def closure_forward_noalloc(self, X):
         """lbmpcd_closure_forward_noalloc: the network on rows of raw features
-        (at most NOALLOC_MAX_ROWS) with the library's own device array for the
-        activations.  Only the output tensor is allocated here, by torch."""
+        (at most NOALLOC_MAX_ROWS) without scratch.  Only the output tensor is
+        allocated here, by torch."""
         X = X.contiguous()
         n = X.shape[0]
         Y = self.torch.empty(n, CLOSURE_NOUT, dtype=self.torch.float32, device=self.device)
