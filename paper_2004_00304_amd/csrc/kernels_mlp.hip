@@ -448,7 +448,6 @@ __global__ void __launch_bounds__(256) k_dw(DwArgs a) {
     f32x16 acc;
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
-#pragma unroll 4
     for (long long kb = kb0; kb < kb1; ++kb) {
         uint4 x = *(const uint4*)pa;
         const uint4 y = *(const uint4*)pb;
@@ -752,36 +751,61 @@ hipError_t closure_features(int lb_fp, const InstDesc* D, int inst, long long ns
     return hipGetLastError();
 }
 
-__global__ void __launch_bounds__(256) k_to_acc(const InstDesc* __restrict__ D, int inst, long long nslab,
-                                                const float* Y, const float* st, const float* uc, double* acc,
+// Network output -> the sample sums of every slab node (acc, when the
+// feedback reads them) and, with do_prof, the profile: each of a node's r fine
+// rows takes one sample at the predicted velocity.  A workgroup takes up to
+// ACC_NODES nodes of one node row, sums them in FP64 and adds its sum to each
+// fine row once (524,288 nodes: 2048 workgroups, 33 thousand FP64 atomics; one
+// add per node, fine row and component were 8.4 million on 64 replicas of 64
+// rows, 450 us).
+constexpr int ACC_NODES = 1024;
+
+__global__ void __launch_bounds__(256) k_to_acc(const InstDesc* __restrict__ D, int inst, const float* __restrict__ Y,
+                                                const float* __restrict__ st, const float* __restrict__ uc, double* acc,
                                                 double* prof, int do_prof) {
-    const long long sn = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (sn >= nslab) return;
+    __shared__ double red[4][4];
     const InstDesc& d = D[inst];
-    double u[3];
-    for (int a = 0; a < 3; ++a)
-        u[a] = (double)Y[sn * NOUT + a] * (double)st[2 * NF + NOUT + a] + (double)st[2 * NF + a] +
-               (double)uc[sn * 3 + a];
-    double* a = acc + (d.acc_off + sn) * 4;
-    a[0] = 1.0; a[1] = u[0]; a[2] = u[1]; a[3] = u[2];
-    if (do_prof) {
-        const int nsy = d.yhi - d.ylo;
-        const int yy = (int)((sn / d.nx) % nsy);
-        const int copy = (int)(sn % NCOPY);
-        for (int i = 0; i < d.r; ++i) {
-            double* gb = prof + (d.prof_off + (long long)copy * d.R + (long long)yy * d.r + i) * 4;
-            atomicAdd(&gb[0], 1.0);
-            atomicAdd(&gb[1], u[0]);
-            atomicAdd(&gb[2], u[1]);
-            atomicAdd(&gb[3], u[2]);
+    const int nsy = d.yhi - d.ylo, yy = blockIdx.y;
+    const long long nrow = (long long)d.nx * d.nz;  // nodes of one node row
+    const long long i0 = (long long)blockIdx.x * ACC_NODES;
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int k = threadIdx.x; k < ACC_NODES; k += 256) {
+        const long long i = i0 + k;
+        if (i >= nrow) break;
+        const long long z = i / d.nx, sn = (z * nsy + yy) * d.nx + (i - z * d.nx);
+        double u[3];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            u[a] = (double)Y[sn * NOUT + a] * (double)st[2 * NF + NOUT + a] + (double)st[2 * NF + a] +
+                   (double)uc[sn * 3 + a];
+            s[1 + a] += u[a];
+        }
+        s[0] += 1.0;
+        if (acc) {
+            double* o = acc + (d.acc_off + sn) * 4;
+            o[0] = 1.0; o[1] = u[0]; o[2] = u[1]; o[3] = u[2];
         }
     }
+    if (!do_prof) return;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) s[q] += __shfl_xor(s[q], o);
+        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6][q] = s[q];
+    }
+    __syncthreads();
+    const int q = threadIdx.x & 3;
+    const double sum = red[0][q] + red[1][q] + red[2][q] + red[3][q];
+    const int copy = (int)((blockIdx.x + blockIdx.y) % NCOPY);
+    for (int i = threadIdx.x >> 2; i < d.r; i += 64)
+        atomicAdd(&prof[(d.prof_off + (long long)copy * d.R + (long long)yy * d.r + i) * 4 + q], sum);
 }
 
-hipError_t closure_to_acc(const InstDesc* D, int inst, long long nslab, const float* Y, const float* stats,
+hipError_t closure_to_acc(const InstDesc* D, int inst, long long nslab, int nsy, const float* Y, const float* stats,
                           const float* uc, double* acc, double* prof, int do_prof, hipStream_t s) {
-    hipLaunchKernelGGL(k_to_acc, dim3(nblk(nslab)), dim3(256), 0, s, D, inst, nslab, Y, stats, uc, acc, prof,
-                       do_prof);
+    if (!acc && !do_prof) return hipSuccess;
+    hipLaunchKernelGGL(k_to_acc, dim3(nblk(nslab / nsy, ACC_NODES), (unsigned)nsy), dim3(256), 0, s, D, inst, Y, stats,
+                       uc, acc, prof, do_prof);
     return hipGetLastError();
 }
 
@@ -815,136 +839,172 @@ __global__ void __launch_bounds__(256) k_band_moments(const InstDesc* __restrict
     o[11] = 0.0f;
 }
 
-// One workgroup of four waves per block of 128 slab nodes, 32 per wave.  The
-// workgroup writes the block's standardised BF16 features into LDS; each
-// wave then runs its 32 rows through the four layers on the matrix cores
-// (v_mfma_f32_32x32x16_bf16, the k steps in the same order as the separate
-// products, so the results are the same), the hidden activations going back
-// into the wave's own rows of the LDS block between layers.  Weights are
-// read from memory (they stay in the caches).  Outputs: the standardised
+// The network on every slab node: one wave takes 32 nodes through all layers
+// on its own rows of LDS, with no barrier, so that the waves of a SIMD overlap
+// one's gathers and products with another's GELUs.  The 271 features are
+// gathered, standardised, rounded and multiplied in chunks of eight stencil
+// entries (80 features, five k steps), which keeps a wave's LDS to one hidden
+// block (8.5 KB) and lets four waves share a SIMD.  The k steps run in the
+// order of k_net's, so the two agree bit for bit.  Outputs: the standardised
 // network output Y and the centre node's LB velocity uc.
-constexpr int FNT = 256;       // threads per workgroup: four waves
-constexpr int FR = 32 * (FNT / 64);  // rows per workgroup, 32 per wave
+//
+// What bounds it: the vector work of 384 GELUs and 271 features per node (the
+// matrix cores are busy a tenth of the time) and the loads' latency.  524,288
+// nodes: 219 us (328 TFLOP/s of network arithmetic); 334 us with all features
+// of 32 rows in LDS (two waves per SIMD, a barrier per layer), 370 us with a
+// wave per 32 columns and its weights in registers (two waves per SIMD, five
+// barriers per tile).  Three waves per SIMD: at four 21 registers spill (235
+// against 227 us before the chunks' loads moved ahead of the products).
+constexpr int FTAB = 24;            // floats per stencil entry of the statistics table
+constexpr int SWAVES = 4;           // waves per workgroup
 
-// One layer for the wave's 32 rows: each k step of 16 loads the rows' inputs
-// from LDS and every column block's weight fragment (one coalesced 1 KiB
-// read per wave), then issues the products.
-template <int K, int NCB>
-__device__ __forceinline__ void mfma_layer(const uint16_t* act, int pitch, const uint16_t* Wf, f32x16 acc[4]) {
-    constexpr int NS = K / 16;
+// NB column blocks of one layer for the wave's 32 rows, NS k steps; weight
+// fragments from the caches, one k step ahead.
+template <int NS, int NB>
+__device__ __forceinline__ void mfma_rows(const uint16_t* act, const uint4* wf, f32x16 (&acc)[NB]) {
     const int lane = threadIdx.x & 63, lr = lane & 31, h = lane >> 5;
+    const uint16_t* ap = act + lr * HPITCH + 8 * h;
+    uint4 w[2][NB];
 #pragma unroll
-    for (int nb = 0; nb < 4; ++nb)
+    for (int nb = 0; nb < NB; ++nb) w[0][nb] = wf[nb * 64];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[nb][r] = 0.0f;
-    const uint4* wf = (const uint4*)Wf + lane;
+    for (int s = 0; s < NS; ++s) {
+        if (s + 1 < NS) {
 #pragma unroll
-    for (int st = 0; st < NS; ++st) {
-        // eight consecutive BF16 inputs as one 16-byte load (rows start at
-        // multiples of 16 bytes)
-        const bf16x8 a = __builtin_bit_cast(bf16x8, *(const uint4*)(act + lr * pitch + st * 16 + 8 * h));
-#pragma unroll
-        for (int nb = 0; nb < NCB; ++nb) {
-            const uint4 b = wf[(st * NCB + nb) * 64];
-            acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, __builtin_bit_cast(bf16x8, b), acc[nb], 0, 0, 0);
+            for (int nb = 0; nb < NB; ++nb) w[(s + 1) & 1][nb] = wf[((s + 1) * NB + nb) * 64];
         }
+        const uint4 x = *(const uint4*)(ap + 16 * s);
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) acc[nb] = mfma16(x, w[s & 1][nb], acc[nb]);
     }
 }
 
-// bias, GELU, BF16 into the wave's rows (C layout: lane holds column lane & 31
-// of each 32-column block, rows 8 (r / 4) + 4 (lane / 32) + r % 4)
-__device__ __forceinline__ void hidden_out(const f32x16 acc[4], const float* bias, uint16_t* act) {
-    const int lane = threadIdx.x & 63, lr = lane & 31, h = lane >> 5;
-#pragma unroll
-    for (int nb = 0; nb < 4; ++nb) {
-        const int col = nb * 32 + lr;
-        const float bc = bias[col];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int row = 8 * (r >> 2) + 4 * h + (r & 3);
-            act[row * HPITCH + col] = to_bf16(gelu(acc[nb][r] + bc));
-        }
-    }
+// Orders the wave's LDS accesses (the LDS serves a wave's accesses in their
+// order; this keeps the compiler from moving them).
+__device__ __forceinline__ void wave_order() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 }
 
-__global__ void __launch_bounds__(FNT) k_mlp_fused(const InstDesc* __restrict__ D, int inst, long long nslab, int y0,
-                                                   int nyb, const float* __restrict__ M, const float* __restrict__ st,
-                                                   const uint16_t* __restrict__ Pf, const float* __restrict__ P32,
-                                                   float* Y, float* uc) {
-    __shared__ uint16_t xs[FR * XPITCH];
-    __shared__ float sinv[NF];     // reciprocals of the features' standard deviations
-    __shared__ int rxyz[3 * FR];   // node coordinates of the block's rows
+__global__ void __launch_bounds__(64 * SWAVES, 3) k_net_slab(const InstDesc* __restrict__ D, int inst, long long nslab,
+                                                             int y0, int nyb, const float* __restrict__ M,
+                                                             const float* __restrict__ st,
+                                                             const uint16_t* __restrict__ Pf,
+                                                             const float* __restrict__ P32, float* __restrict__ Y,
+                                                             float* __restrict__ uc) {
+    __shared__ __align__(16) uint16_t rows[SWAVES * 32 * HPITCH];
+    __shared__ __align__(16) float tab[28 * FTAB];  // per stencil entry: 10 means (pad 2), 10 reciprocal deviations (pad 2)
     const InstDesc& d = D[inst];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const long long r0 = (long long)blockIdx.x * FR;
-    const int nsy = d.yhi - d.ylo;
-    for (int k = tid; k < NF; k += FNT) sinv[k] = 1.0f / st[NF + k];
-    // the divisions by the channel's sizes once per row, not per stencil entry
-    for (int r = tid; r < FR; r += FNT) {
-        const long long sn = r0 + r < nslab ? r0 + r : 0;
-        rxyz[3 * r] = (int)(sn % d.nx);
-        rxyz[3 * r + 1] = d.ylo + (int)((sn / d.nx) % nsy);
-        rxyz[3 * r + 2] = (int)(sn / ((long long)d.nx * nsy));
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 31, h = lane >> 5;
+    for (int k = threadIdx.x; k < NF; k += 64 * SWAVES) {
+        tab[(k / 10) * FTAB + k % 10] = st[k];
+        tab[(k / 10) * FTAB + 12 + k % 10] = 1.0f / st[NF + k];
     }
     __syncthreads();
-    auto band_index = [&](int r, int dx, int dy, int dz) {
-        const int x = rxyz[3 * r], y = rxyz[3 * r + 1], z = rxyz[3 * r + 2];
-        int xx = x + dx; if (xx < 0) xx += d.nx; else if (xx >= d.nx) xx -= d.nx;
-        int zz = z + dz; if (zz < 0) zz += d.nz; else if (zz >= d.nz) zz -= d.nz;
-        int yy = y + dy; yy = yy < 0 ? 0 : (yy >= d.ny ? d.ny - 1 : yy);
-        return ((long long)zz * nyb + (yy - y0)) * d.nx + xx;
-    };
-    // standardised features of the block: stencil entry s of row r (lanes of
-    // a wave take consecutive rows of one stencil entry)
-#pragma unroll 4
-    for (int it = tid; it < FR * 27; it += FNT) {
-        const int r = it % FR, s = it / FR;
-        const long long sn = r0 + r;
-        uint16_t* xr = xs + r * XPITCH + s * 10;
-        if (sn >= nslab) {
-            for (int q = 0; q < 10; ++q) xr[q] = 0;
-            continue;
-        }
-        const float* m = M + band_index(r, s % 3 - 1, (s / 3) % 3 - 1, s / 9 - 1) * BMS;
-        for (int q = 0; q < 10; ++q) {
-            const int k = s * 10 + q;
-            xr[q] = to_bf16((m[q] - st[k]) * sinv[k]);
-        }
-    }
-    for (int r = tid; r < FR; r += FNT) {
-        const long long sn = r0 + r;
-        uint16_t* xr = xs + r * XPITCH;
-        for (int q = NF - 1; q < NFP; ++q) xr[q] = 0;
-        if (sn >= nslab) continue;
-        const float* m = M + band_index(r, 0, 0, 0) * BMS;
-        xr[NF - 1] = to_bf16((m[10] - st[NF - 1]) * sinv[NF - 1]);
-        for (int a = 0; a < 3; ++a) uc[sn * 3 + a] = m[1 + a];
-    }
-    __syncthreads();
-
-    uint16_t* own = xs + wave * 32 * XPITCH;  // this wave's rows; hidden blocks reuse them
+    const long long r0 = ((long long)blockIdx.x * SWAVES + wave) * 32;
+    if (r0 >= nslab) return;
+    const long long sn = r0 + lr;
+    const bool in = sn < nslab;
+    const int nsy = d.yhi - d.ylo, nx = d.nx, ny = d.ny, nz = d.nz;
+    const long long sc = in ? sn : 0, rw = sc / nx;
+    const int x = (int)(sc - rw * nx), y = d.ylo + (int)(rw % nsy), z = (int)(rw / nsy);
+    uint16_t* act = rows + wave * 32 * HPITCH;
+    const uint4* wf = (const uint4*)Pf + lane;
     f32x16 acc[4];
-    mfma_layer<NFP, 4>(own, XPITCH, Pf + FRAG_L1, acc);
-    __syncthreads();
-    hidden_out(acc, P32 + OFF_B1, own);
-    __syncthreads();
-    mfma_layer<NH, 4>(own, HPITCH, Pf + FRAG_L2, acc);
-    __syncthreads();
-    hidden_out(acc, P32 + OFF_B2, own);
-    __syncthreads();
-    mfma_layer<NH, 4>(own, HPITCH, Pf + FRAG_L3, acc);
-    __syncthreads();
-    hidden_out(acc, P32 + OFF_B3, own);
-    __syncthreads();
-    mfma_layer<NH, 1>(own, HPITCH, Pf + FRAG_L4, acc);
-    const int lr = lane & 31, h = lane >> 5;
-    if (lr < NOUT) {
-        const float bc = P32[OFF_B4 + lr];
+    auto clear = [&] {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const long long sn = r0 + wave * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
-            if (sn < nslab) Y[sn * NOUT + lr] = acc[0][r] + bc;
+        for (int nb = 0; nb < 4; ++nb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[nb][r] = 0.0f;
+    };
+    clear();
+    // stencil entry e of the lane's node into columns c..c + 9 of its row
+    auto node = [&](int e) {
+        const int dx = e % 3 - 1, dy = (e / 3) % 3 - 1, dz = e / 9 - 1;
+        int xx = x + dx; if (xx < 0) xx += nx; else if (xx >= nx) xx -= nx;
+        int zz = z + dz; if (zz < 0) zz += nz; else if (zz >= nz) zz -= nz;
+        int yy = y + dy; yy = yy < 0 ? 0 : (yy >= ny ? ny - 1 : yy);
+        return (const float4*)(M + (((long long)zz * nyb + (yy - y0)) * nx + xx) * BMS);
+    };
+    auto put = [&](const float4& m0, const float4& m1, const float4& m2, int e, int c) {
+        const float m[10] = {m0.x, m0.y, m0.z, m0.w, m1.x, m1.y, m1.z, m1.w, m2.x, m2.y};
+        const float* t = tab + FTAB * e;
+        uint32_t* o = (uint32_t*)(act + lr * HPITCH + c);
+#pragma unroll
+        for (int q = 0; q < 10; q += 2) {
+            const uint32_t lo = to_bf16((m[q] - t[q]) * t[12 + q]);
+            const uint32_t hi = to_bf16((m[q + 1] - t[q + 1]) * t[13 + q]);
+            o[q / 2] = in ? lo | (hi << 16) : 0u;
         }
+    };
+    // three chunks of eight entries, then the last three, the shear rate of
+    // the node itself and zeros; lane half h takes the entries of its parity.
+    // Each chunk's nodes are loaded before the products of the chunk before.
+    float4 m[4][3];
+    auto load = [&](int ch) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int e = 8 * ch + 2 * i + h;
+            const float4* p = node(e < 27 ? e : 13);
+            m[i][0] = p[0]; m[i][1] = p[1]; m[i][2] = p[2];
+        }
+    };
+    load(0);
+#pragma unroll 1
+    for (int ch = 0; ch < 3; ++ch) {
+        wave_order();
+#pragma unroll
+        for (int i = 0; i < 4; ++i) put(m[i][0], m[i][1], m[i][2], 8 * ch + 2 * i + h, 10 * (2 * i + h));
+        wave_order();
+        load(ch + 1);
+        mfma_rows<5, 4>(act, wf + (FRAG_L1 / 8 + ch * 5 * 4 * 64), acc);
+    }
+    wave_order();
+    put(m[0][0], m[0][1], m[0][2], 24 + h, 10 * h);
+    if (h == 0) {
+        put(m[1][0], m[1][1], m[1][2], 26, 20);
+    } else {
+        uint32_t* o = (uint32_t*)(act + lr * HPITCH + 30);
+        const float* t = tab + FTAB * 27;
+        o[0] = in ? (uint32_t)to_bf16((m[1][2].z - t[0]) * t[12]) : 0u;
+#pragma unroll
+        for (int q = 1; q < 9; ++q) o[q] = 0u;
+        if (in) {
+            uc[sn * 3] = m[1][0].y;
+            uc[sn * 3 + 1] = m[1][0].z;
+            uc[sn * 3 + 2] = m[1][0].w;
+        }
+    }
+    wave_order();
+    mfma_rows<3, 4>(act, wf + (FRAG_L1 / 8 + 15 * 4 * 64), acc);
+    auto hidden = [&](long long ob) {
+        wave_order();
+#pragma unroll
+        for (int nb = 0; nb < 4; ++nb) {
+            const float bias = P32[ob + 32 * nb + lr];
+            float v[16];
+#pragma unroll
+            for (int r = 0; r < 16; ++r) v[r] = gelu(acc[nb][r] + bias);
+            put_cols<false>(v, 32 * nb + lr, act, HPITCH, nullptr, 0, NH);
+        }
+        wave_order();
+        clear();
+    };
+    hidden(OFF_B1);
+    mfma_rows<NH / 16, 4>(act, wf + FRAG_L2 / 8, acc);
+    hidden(OFF_B2);
+    mfma_rows<NH / 16, 4>(act, wf + FRAG_L3 / 8, acc);
+    hidden(OFF_B3);
+    f32x16 yo[1];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) yo[0][r] = 0.0f;
+    mfma_rows<NH / 16, 1>(act, wf + FRAG_L4 / 8, yo);
+    if (lr >= NOUT) return;
+    const float b4 = P32[OFF_B4 + lr];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const long long row = r0 + 8 * (r >> 2) + 4 * h + (r & 3);
+        if (row < nslab) Y[row * NOUT + lr] = yo[0][r] + b4;
     }
 }
 
@@ -959,8 +1019,8 @@ hipError_t closure_predict(int lb_fp, const InstDesc* D, int inst, long long nsl
                            y0, nyb, M);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_mlp_fused, dim3(nblk(nslab, FR)), dim3(FNT), 0, s, D, inst, nslab, y0, nyb, M, stats, Pf,
-                       P32, Y, uc);
+    hipLaunchKernelGGL(k_net_slab, dim3(nblk(nslab, 32 * SWAVES)), dim3(64 * SWAVES), 0, s, D, inst, nslab, y0, nyb, M,
+                       stats, Pf, P32, Y, uc);
     return hipGetLastError();
 }
 

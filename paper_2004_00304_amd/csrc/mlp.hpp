@@ -102,8 +102,9 @@ hipError_t mlp_stats(const float* X, const float* Y, long long n, double* sums, 
 hipError_t closure_features(int lb_fp, const InstDesc* D, int inst, long long nslab, const void* f,
                             double* facc, const float* stats, uint16_t* Xb, float* uc, hipStream_t s);
 // Network output -> feedback sums (count 1, predicted velocity) of every slab
-// node; with do_prof also into the profile accumulators.
-hipError_t closure_to_acc(const InstDesc* D, int inst, long long nslab, const float* Y, const float* stats,
+// node (unless acc is null); with do_prof also into the profile accumulators.
+// nsy: node rows of the slab.
+hipError_t closure_to_acc(const InstDesc* D, int inst, long long nslab, int nsy, const float* Y, const float* stats,
                           const float* uc, double* acc, double* prof, int do_prof, hipStream_t s);
 // Fused inference of every slab node of the current populations: the moments
 // and shear rate of the band rows [y0, y0 + nyb) into M (nband x 12 floats),
