@@ -750,7 +750,10 @@ __device__ __forceinline__ void particle_tile(const PArgs<PT>& A, long long T, u
                     }
                 }
                 if (A.do_prof) {
-                    const int aj = J - wj0;
+                    int aj = J - wj0;
+                    // a particle re-wrapped across the slab samples a row next
+                    // to the tile modulo the slab's rows
+                    if (aj < 0) aj += d.R; else if (aj >= wnj) aj -= d.R;
                     if (wj_ok && aj >= 0 && aj < wnj) {
 #pragma unroll
                         for (int q = 0; q < DIM + 1; ++q) sum_lds<DET>(&wprof[4 * NREP * aj + wrep + q], vals[q]);
@@ -937,7 +940,9 @@ __device__ __forceinline__ void particle_tile(const PArgs<PT>& A, long long T, u
                         else sum[q] += wprof[4 * (NREP * i + r) + q];
                     }
                 if (DET ? isum[0] == 0ull : sum[0] == 0.0) continue;
-                const int J = wj0 + i;
+                int J = wj0 + i;
+                if (J < 0) J += d.R; else if (J >= d.R) J -= d.R;
+                if (J < 0 || J >= d.R) continue;  // windows of more rows than the slab: never sampled
                 double* gb = A.prof + (d.prof_off + (long long)copy * d.R + J) * 4;
 #pragma unroll
                 for (int q = 0; q < DIM + 1; ++q) {
