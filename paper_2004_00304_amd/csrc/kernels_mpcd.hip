@@ -5,7 +5,7 @@
 
 namespace lbmpcd {
 
-size_t particle_lds_bytes(int, int, int) { return LDS_HDR + LDS_WIN + LDS_COLL; }
+size_t particle_lds_bytes(int, int, int) { return LDS_HDR + LDS_UNI; }
 
 namespace {
 struct PlainModes {

@@ -228,16 +228,24 @@ __device__ __forceinline__ double sum_read(const double* p) {
 }
 
 // LDS carve-up (bytes): header (counters and the table of destination tiles),
-// sample windows, collision arrays and the tile's window of buffer-cell LB
-// velocities.
+// then one region that holds the collision arrays and the tile's window of
+// buffer-cell LB velocities first, and the sample windows afterwards.
 constexpr int NHASH_BITS = 6;
 constexpr int NHASH = 1 << NHASH_BITS;
 constexpr size_t LDS_HDR = 1088;  // >= 4 * (4 + 3 * NHASH + 2), a multiple of 16
-// Sample windows hold NREP interleaved replicas of every bin (lane l adds
-// into replica l mod NREP), so that the lanes of a wave, which mostly sample
-// the same one or two nodes, spread their FP64 atomics over more banks.
+// Node sample window: NREP interleaved replicas of every bin (lane l adds into
+// replica l mod NREP), so that the lanes of a wave, which mostly sample the
+// same few nodes, spread their FP64 atomics over more banks.  Profile window:
+// a wave's particles lie in two or three fine rows, so every row has a slot per
+// lane (per pair of lanes in windows of more than eight rows), component by
+// component, and no two lanes of a wave meet on an address; with four
+// replicas per row five did (thin film, a sampling launch: 6.83 -> 6.66 ms;
+// without the barrier that the shared region saves every launch, 3D channel
+// step 12.55 -> 12.46 ms).
 constexpr int NREP = 4;
-constexpr size_t LDS_WIN = (size_t)(MAX_WIN + MAX_WJ) * NREP * 4 * sizeof(double);
+constexpr int PROF_SLOTS = 512;  // rows x slots per row of the profile window
+static_assert(MAX_WJ * 32 <= PROF_SLOTS, "profile window rows");
+constexpr size_t LDS_WIN = ((size_t)MAX_WIN * NREP * 4 + (size_t)PROF_SLOTS * 4) * sizeof(double);
 // The exchange reads the LB velocity of a buffer particle's fine cell.  A
 // particle binned into shifted cell i (shift in [0, a)) sits in unshifted
 // fine cell i - 1 or i, so the particles of a tile of Tx x Ty x Tz cells read
@@ -246,6 +254,7 @@ constexpr size_t LDS_WIN = (size_t)(MAX_WIN + MAX_WJ) * NREP * 4 * sizeof(double
 // and the collision instead of stalling the exchange.
 constexpr size_t LDS_COLL = (size_t)MAX_NCT * 4 + (size_t)MAX_NCT * 9 * sizeof(double) +
                             (size_t)MAX_UFC * 3 * sizeof(double);
+constexpr size_t LDS_UNI = LDS_COLL > LDS_WIN ? LDS_COLL : LDS_WIN;
 constexpr uint32_t DROP_SLOT = 0x7FFFFFFFu;  // never a slot: the slot total stays below it
 constexpr long long OVF_GRID = 128;           // workgroups of the overflow pass
 static_assert(4 * (4 + 3 * NHASH + 2) <= (int)LDS_HDR, "LDS header too small");
@@ -277,9 +286,9 @@ __device__ __forceinline__ void particle_tile(const PArgs<PT>& A, long long T, u
     uint32_t* hkey = wstat + 4;                 // [NHASH] destination tiles (local index)
     uint32_t* hcnt = hkey + NHASH;              // [NHASH + 1] particles per destination
     uint32_t* gbase = hcnt + NHASH + 1;         // [NHASH + 1] reserved run start
-    double* wacc = (double*)(smem + LDS_HDR);   // [MAX_WIN][NREP][4] node sample window
-    double* wprof = wacc + MAX_WIN * NREP * 4;  // [MAX_WJ][NREP][4] profile window
-    unsigned char* uni = smem + LDS_HDR + LDS_WIN;
+    unsigned char* uni = smem + LDS_HDR;
+    double* wacc = (double*)uni;                // [MAX_WIN][NREP][4] node sample window
+    double* wprof = wacc + MAX_WIN * NREP * 4;  // [4][rows][slots] profile window
     uint32_t* ccnt = (uint32_t*)uni;                 // [MAX_NCT]
     double* csv = (double*)(uni + MAX_NCT * 4);      // [MAX_NCT][3]
     double* cvcm = csv + MAX_NCT * 3;                // [MAX_NCT][3]
@@ -360,6 +369,10 @@ __device__ __forceinline__ void particle_tile(const PArgs<PT>& A, long long T, u
     }
     if (tid == 0 && n > (uint32_t)(3 * cap / 4)) atomicMax(&A.stats->max_fill, n);
     if (tid < 4) wstat[tid] = 0u;
+    if constexpr (STREAM) {
+        for (int i = tid; i < NHASH; i += NT) hkey[i] = BAD_SLOT;
+        for (int i = tid; i <= NHASH; i += NT) hcnt[i] = 0u;
+    }
     // window of fine cells (origin one cell below the tile on each axis);
     // only buffer rows are copied, and only for tiles that reach them
     if constexpr (STREAM) {
@@ -562,15 +575,10 @@ __device__ __forceinline__ void particle_tile(const PArgs<PT>& A, long long T, u
         const bool win_ok = wnx * wny * wnz <= MAX_WIN;
         const int wj0 = (ty << d.lTy) - 2, wnj = d.Ty + 4;
         const bool wj_ok = wnj <= MAX_WJ;
+        const int wslots = wnj <= PROF_SLOTS / 64 ? 64 : 32;
         const int copy = (int)(lt % (uint32_t)NCOPY);
-        if (A.do_fb && win_ok)
-            for (int i = tid; i < wnx * wny * wnz * NREP * 4; i += NT) wacc[i] = 0.0;
-        if (A.do_prof && wj_ok)
-            for (int i = tid; i < wnj * NREP * 4; i += NT) wprof[i] = 0.0;
-        const int wrep = 4 * (lane & (NREP - 1));
-        for (int i = tid; i < NHASH; i += NT) hkey[i] = BAD_SLOT;
-        for (int i = tid; i <= NHASH; i += NT) hcnt[i] = 0u;
-        __syncthreads();
+        // the collision's barriers cover the tables written at the start
+        if constexpr (!COLL) __syncthreads();
 
         const double ylo_d = (double)d.ylo, yhi_d = (double)d.yhi;
         // the slab faces are integers, exact in either precision, so the
@@ -722,6 +730,15 @@ __device__ __forceinline__ void particle_tile(const PArgs<PT>& A, long long T, u
         // loops over a thread's particles are split by task so that fewer
         // per-tile constants are live at once
         if (A.do_fb | A.do_prof) {
+            // the windows take the place of the collision arrays and the
+            // LB velocities
+            __syncthreads();
+            if (A.do_fb && win_ok)
+                for (int i = tid; i < wnx * wny * wnz * NREP * 4; i += NT) wacc[i] = 0.0;
+            if (A.do_prof && wj_ok)
+                for (int i = tid; i < wnj * wslots * 4; i += NT) wprof[i] = 0.0;
+            __syncthreads();
+            const int wrep = 4 * (lane & (NREP - 1));
 #pragma unroll
             for (int k = 0; k < PPT; ++k) {
                 if (!valid[k]) continue;
@@ -756,7 +773,8 @@ __device__ __forceinline__ void particle_tile(const PArgs<PT>& A, long long T, u
                     if (aj < 0) aj += d.R; else if (aj >= wnj) aj -= d.R;
                     if (wj_ok && aj >= 0 && aj < wnj) {
 #pragma unroll
-                        for (int q = 0; q < DIM + 1; ++q) sum_lds<DET>(&wprof[4 * NREP * aj + wrep + q], vals[q]);
+                        for (int q = 0; q < DIM + 1; ++q)
+                            sum_lds<DET>(&wprof[(q * wnj + aj) * wslots + (lane & (wslots - 1))], vals[q]);
                     } else {
                         double* gb = A.prof + (d.prof_off + (long long)copy * d.R + J) * 4;
 #pragma unroll
@@ -929,26 +947,29 @@ __device__ __forceinline__ void particle_tile(const PArgs<PT>& A, long long T, u
             }
         }
         if (A.do_prof && wj_ok) {
-            for (int i = tid; i < wnj; i += NT) {
-                double sum[4] = {0.0, 0.0, 0.0, 0.0};
-                [[maybe_unused]] unsigned long long isum[4] = {0ull, 0ull, 0ull, 0ull};
-#pragma unroll
-                for (int r = 0; r < NREP; ++r)
-#pragma unroll
-                    for (int q = 0; q < DIM + 1; ++q) {
-                        if constexpr (DET) isum[q] += ((const unsigned long long*)wprof)[4 * (NREP * i + r) + q];
-                        else sum[q] += wprof[4 * (NREP * i + r) + q];
-                    }
-                if (DET ? isum[0] == 0ull : sum[0] == 0.0) continue;
-                int J = wj0 + i;
-                if (J < 0) J += d.R; else if (J >= d.R) J -= d.R;
-                if (J < 0 || J >= d.R) continue;  // windows of more rows than the slab: never sampled
-                double* gb = A.prof + (d.prof_off + (long long)copy * d.R + J) * 4;
-#pragma unroll
-                for (int q = 0; q < DIM + 1; ++q) {
-                    if constexpr (DET) atomicAdd((unsigned long long*)&gb[q], isum[q]);
-                    else gl_add(&gb[q], sum[q]);
+            // 16 lanes per row and component; the four components of a row
+            // leave in one instruction
+            for (int i = tid >> 4; i < wnj * 4; i += NT / 16) {
+                const int q = i & 3, row = i >> 2;
+                if (DIM == 2 && q == 3) continue;
+                const double* w = wprof + (q * wnj + row) * wslots;
+                double sum = 0.0;
+                [[maybe_unused]] unsigned long long isum = 0ull;
+                for (int j = tid & 15; j < wslots; j += 16) {
+                    if constexpr (DET) isum += ((const unsigned long long*)w)[j];
+                    else sum += w[j];
                 }
+#pragma unroll
+                for (int o = 8; o > 0; o >>= 1) {
+                    if constexpr (DET) isum += __shfl_xor(isum, o);
+                    else sum += __shfl_xor(sum, o);
+                }
+                if ((tid & 15) != 0 || (DET ? isum == 0ull : sum == 0.0)) continue;
+                int J = wj0 + row;
+                if (J < 0) J += d.R; else if (J >= d.R) J -= d.R;
+                double* gb = A.prof + (d.prof_off + (long long)copy * d.R + J) * 4 + q;
+                if constexpr (DET) atomicAdd((unsigned long long*)gb, isum);
+                else gl_add(gb, sum);
             }
         }
         if (tid == 0) {
