@@ -50,7 +50,6 @@ struct lbmpcd_ctx {
     size_t prof_bytes = 0, acc_bytes = 0;
     long long total_nodes = 0, total_band = 0, total_ufine = 0, total_tiles = 0, total_slots = 0,
               total_particles = 0, total_slab = 0;
-    size_t lds = 0;
     int cap_max = 0;              // largest tile capacity
     int exp_max = 0;              // largest expected tile occupancy
     bool split_ok = false;        // the particle launch may take the six-slot form
@@ -59,7 +58,6 @@ struct lbmpcd_ctx {
     int ce_bit = 0;               // 8 for the Chapman-Enskog exchange (particle kernel mode bit)
     int det_bit = 0;              // 16 for the deterministic mode (particle kernel mode bit)
     int xcd_blocked = 1;          // XCD-blocked tile order of the particle kernel
-    long long cstride = 0;        // bytes between the component arrays of a particle buffer
     long long t = 0;
     bool pending = false, sampling = false, any_feedback = false;
     long long sampled_steps = 0;
@@ -350,7 +348,7 @@ static int default_wg_threads(int part_fp, int cap_max, int exp_max, long long t
 struct Layout {
     size_t desc, tile_inst, f0, f1, ub, uf, tb, tf, acc, fbu, prof, fill0, fill1, stats, ovf, clock, shifts, scratch, end;
     size_t cl_P, cl_Pf, cl_G, cl_m, cl_v, cl_stats, cl_sums, cl_loss, cl_facc, cl_nm, cl_uc, cl_M, cl_Y;
-    size_t part[2];       // particle buffer: 2 dim component arrays of cstride bytes, then ids
+    size_t part[2];       // particle buffers: N16 arrays of cstride bytes, then one of LAST bytes a slot (PStore)
     size_t cstride;
     size_t acc_bytes, prof_bytes, scratch_bytes;
 };
@@ -416,7 +414,7 @@ int build(const lbmpcd_params* p, int n, std::vector<InstDesc>& D, Layout& L, lo
     if (slots >= 0x7FFFFFFFLL) { msg = "too many particle slots for 31-bit slot indices"; return LBMPCD_E_INVALID; }
     tot[0] = node; tot[1] = band; tot[2] = ufine; tot[3] = tiles; tot[4] = slots; tot[5] = parts; tot[6] = slab;
     const int dim = p[0].dim;
-    const size_t lbw = p[0].lb_fp == 64 ? 8 : 4, pw = p[0].part_fp == 64 ? 8 : 4;
+    const size_t lbw = p[0].lb_fp == 64 ? 8 : 4;
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t at = o; o = align_up(o + std::max<size_t>(bytes, 1), 256); return at; };
     L.desc = take(sizeof(InstDesc) * n);
@@ -435,8 +433,10 @@ int build(const lbmpcd_params* p, int n, std::vector<InstDesc>& D, Layout& L, lo
     L.prof = take(L.prof_bytes);
     L.fill0 = take(4 * (size_t)tiles);
     L.fill1 = take(4 * (size_t)tiles);
-    L.cstride = align_up((size_t)slots * pw, 256);
-    for (int b = 0; b < 2; ++b) L.part[b] = take(2 * (size_t)dim * L.cstride + (size_t)slots * 4);
+    const int pfp = p[0].part_fp;
+    L.cstride = align_up((size_t)slots * 16, PART_ALIGN);
+    for (int b = 0; b < 2; ++b)
+        L.part[b] = take(part_n16(dim, pfp) * L.cstride + (size_t)slots * part_last(dim, pfp));
     L.stats = take(sizeof(DevStats));
     L.ovf = take(4 * ((size_t)tiles + 2));
     L.clock = take(sizeof(long long));
@@ -538,7 +538,7 @@ int finalize(lbmpcd_ctx* c) {
     L.tile_inst = c->d_tile_inst; L.ufine = c->uf; L.tfine = c->tf; L.acc = c->acc; L.prof = c->prof;
     L.stats = c->stats; L.clock = c->clock; L.shifts = c->shifts;
     L.coll_dt = 0; L.coll_s = c->S - 1; L.str_s = 0;
-    L.diag_inst = -1; L.cell_vcm = nullptr; L.lds_bytes = c->lds; L.cap_max = c->cap_max; L.ovf = c->split_ok ? c->ovf : nullptr; L.exp_max = c->exp_max; L.wg_threads = c->wg_threads; L.cstride = c->cstride; L.xcd_blocked = c->xcd_blocked;
+    L.diag_inst = -1; L.cell_vcm = nullptr; L.cap_max = c->cap_max; L.ovf = c->split_ok ? c->ovf : nullptr; L.exp_max = c->exp_max; L.wg_threads = c->wg_threads; L.xcd_blocked = c->xcd_blocked;
     HIPCHK(c, launch_particles(L, c->stream));
     c->pending = false;
     return 0;
@@ -667,15 +667,8 @@ int lbmpcd_init(const lbmpcd_params* p, int32_t n_inst, void* dev_workspace, siz
     c->prof_bytes = L.prof_bytes;
     c->fill[0] = (uint32_t*)(c->ws + L.fill0);
     c->fill[1] = (uint32_t*)(c->ws + L.fill1);
-    c->cstride = (long long)L.cstride;
-    for (int b = 0; b < 2; ++b) {
-        unsigned char* pb = (unsigned char*)(c->ws + L.part[b]);
-        for (int k = 0; k < 3; ++k) {
-            c->part[b].pos[k] = k < c->dim ? pb + (size_t)k * L.cstride : nullptr;
-            c->part[b].vel[k] = k < c->dim ? pb + (size_t)(c->dim + k) * L.cstride : nullptr;
-        }
-        c->part[b].id = (uint32_t*)(pb + (size_t)2 * c->dim * L.cstride);
-    }
+    for (int b = 0; b < 2; ++b)
+        c->part[b] = PartBuf{(unsigned char*)(c->ws + L.part[b]), (long long)L.cstride};
     c->stats = (DevStats*)(c->ws + L.stats);
     c->ovf = (uint32_t*)(c->ws + L.ovf);
     c->clock = (long long*)(c->ws + L.clock);
@@ -712,7 +705,6 @@ int lbmpcd_init(const lbmpcd_params* p, int32_t n_inst, void* dev_workspace, siz
     // only on grids large enough to gain from it
     c->split_ok = c->wg_threads == 256 && six_slot_fits(cap_max, c->exp_max) &&
                   (p[0].wg_threads == 256 || c->total_tiles >= SPLIT_MIN_TILES);
-    c->lds = particle_lds_bytes(c->dim, c->part_fp, cap_max);
     c->coll_bit = p[0].collision == 1 ? 4 : 0;
     c->det_bit = (p[0].mpcd && p[0].deterministic) ? 16 : 0;
     c->xcd_blocked = p[0].schedule == 0 ? 1 : 0;
@@ -825,7 +817,7 @@ int enqueue_one_step(lbmpcd_ctx* c, hipStream_t s) {
                 // samples are taken in the last MPCD step of the LB step
                 L.do_fb = (c->any_feedback && sub == c->S - 1) ? 1 : 0;
                 L.do_prof = (c->sampling && sub == c->S - 1) ? 1 : 0;
-                L.diag_inst = -1; L.cell_vcm = nullptr; L.lds_bytes = c->lds; L.cap_max = c->cap_max; L.ovf = c->split_ok ? c->ovf : nullptr; L.exp_max = c->exp_max; L.wg_threads = c->wg_threads; L.cstride = c->cstride; L.xcd_blocked = c->xcd_blocked;
+                L.diag_inst = -1; L.cell_vcm = nullptr; L.cap_max = c->cap_max; L.ovf = c->split_ok ? c->ovf : nullptr; L.exp_max = c->exp_max; L.wg_threads = c->wg_threads; L.xcd_blocked = c->xcd_blocked;
                 HIPCHK(c, timed(c, 3, [&] { return launch_particles(L, s); }));
                 c->pcur ^= 1;
                 c->pending = true;
@@ -961,14 +953,15 @@ int produce(lbmpcd_ctx* c, int32_t field, int32_t inst, void* dst, size_t nbytes
             // unless the pre-collision values are asked for
             if (field == LBMPCD_PART_VEL)
                 if (int e = finalize(c)) return e;
-            HIPCHK(c, launch_gather(c->dim, c->part_fp, c->d_desc, inst, c->part[c->pcur], c->fill[c->pcur],
-                                    field == LBMPCD_PART_POS ? (double*)dst : nullptr,
-                                    field != LBMPCD_PART_POS ? (double*)dst : nullptr, nullptr, slots, tl, sl, s));
+            HIPCHK(c, launch_gather(c->dim, c->part_fp, c->d_desc, inst, d, c->part[c->pcur],
+                                    c->fill[c->pcur], field == LBMPCD_PART_POS ? (double*)dst : nullptr,
+                                    field != LBMPCD_PART_POS ? (double*)dst : nullptr, nullptr,
+                                    c->part[c->pcur ^ 1].b, tl, sl, s));
             return 0;
         case LBMPCD_CELL_ID:
             if (c->t == 0) return fail(c, LBMPCD_E_STATE, "no binning before the first step");
-            HIPCHK(c, launch_gather(c->dim, c->part_fp, c->d_desc, inst, c->part[c->pcur], c->fill[c->pcur],
-                                    nullptr, nullptr, (int*)dst, slots, tl, sl, s));
+            HIPCHK(c, launch_gather(c->dim, c->part_fp, c->d_desc, inst, d, c->part[c->pcur],
+                                    c->fill[c->pcur], nullptr, nullptr, (int*)dst, nullptr, tl, sl, s));
             return 0;
         case LBMPCD_CELL_COUNT:
             if (c->t == 0) return fail(c, LBMPCD_E_STATE, "no binning before the first step");
@@ -1003,7 +996,7 @@ int produce(lbmpcd_ctx* c, int32_t field, int32_t inst, void* dst, size_t nbytes
             L.tile_inst = c->d_tile_inst; L.ufine = c->uf; L.tfine = c->tf; L.acc = c->acc; L.prof = c->prof;
             L.stats = c->stats; L.clock = c->clock; L.shifts = c->shifts; L.shifts = c->shifts;
             L.coll_dt = 0; L.coll_s = c->S - 1; L.str_s = 0;
-            L.diag_inst = inst; L.cell_vcm = (double*)dst; L.lds_bytes = c->lds; L.cap_max = c->cap_max; L.ovf = c->split_ok ? c->ovf : nullptr; L.exp_max = c->exp_max; L.wg_threads = c->wg_threads; L.cstride = c->cstride; L.xcd_blocked = c->xcd_blocked;
+            L.diag_inst = inst; L.cell_vcm = (double*)dst; L.cap_max = c->cap_max; L.ovf = c->split_ok ? c->ovf : nullptr; L.exp_max = c->exp_max; L.wg_threads = c->wg_threads; L.xcd_blocked = c->xcd_blocked;
             HIPCHK(c, launch_particles(L, s));
             return 0;
         }
@@ -1097,7 +1090,7 @@ int lbmpcd_set_state(lbmpcd_ctx* c, int32_t field, int32_t inst, const void* src
     }
     HIPCHK(c, launch_set_field(c->dim, c->part_fp, c->d_desc, inst, c->part[c->pcur], c->fill[c->pcur],
                                field == LBMPCD_PART_POS ? 0 : 1, (const double*)dsrc,
-                               d.ntiles * (long long)d.cap, s));
+                               d.ntiles, s));
     HIPCHK(c, hipStreamSynchronize(s));
     return 0;
 }
@@ -1261,8 +1254,8 @@ int lbmpcd_closure_collect(lbmpcd_ctx* c, int32_t lb_steps, float* X, float* Y) 
         if (c->sampling) c->sampled_steps++;
         // the samples are taken from the collided state
         if (int e2 = finalize(c)) return e2;
-        HIPCHK(c, closure_node_moments(c->part_fp, c->d_desc, 0, d.ntiles, c->part[c->pcur].pos[0],
-                                       c->cstride, c->fill[c->pcur], c->cl_nm, c->stream));
+        HIPCHK(c, closure_node_moments(c->part_fp, c->d_desc, 0, d.ntiles, c->part[c->pcur], c->fill[c->pcur],
+                                       c->cl_nm, c->stream));
     }
     HIPCHK(c, closure_collect_finish(c->cl_nslab, lb_steps, d.mass, c->cl_facc, c->cl_nm, X, Y, c->stream));
     return 0;

@@ -243,14 +243,6 @@ struct DevStats {
                                     // turned non-finite, band nodes with rho <= 0 or non-finite moments
 };
 
-// Particle arrays of one buffer: positions, velocities, ids (slot-indexed).
-template <typename PT>
-struct PartPtrs {
-    PT* pos[3];
-    PT* vel[3];
-    uint32_t* id;
-};
-
 __device__ __forceinline__ int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
 
 // One coordinate of the shifted-grid cell, floor((x - lo + shift) * r),

@@ -12,6 +12,7 @@
 
 #include "common.hpp"
 #include "gelu.hpp"
+#include "launch.hpp"
 #include "mlp.hpp"
 
 namespace lbmpcd {
@@ -1049,8 +1050,7 @@ constexpr int NMREP = 8;    // 40 KB of LDS with 10 FP64 sums per node and repli
 
 template <typename PT>
 __global__ void __launch_bounds__(256) k_node_moments(const InstDesc* __restrict__ D, int inst,
-                                                      const unsigned char* pos0, long long cs,
-                                                      const uint32_t* fill, double* nm) {
+                                                      PartBuf P, const uint32_t* fill, double* nm) {
     __shared__ double win[NM_WIN * NMREP * 10];
     const InstDesc& d = D[inst];
     const uint32_t T = blockIdx.x;  // tile within the channel
@@ -1066,15 +1066,16 @@ __global__ void __launch_bounds__(256) k_node_moments(const InstDesc* __restrict
     for (int i = threadIdx.x; i < nwin * NMREP * 10; i += 256) win[i] = 0.0;
     __syncthreads();
     const uint32_t n = min(fill[d.tile_off + T], (uint32_t)d.cap);
-    const PT* c[6];
-    for (int q = 0; q < 6; ++q) c[q] = (const PT*)(pos0 + q * cs) + d.slot_off + (long long)T * d.cap;
     const int A[6] = {0, 1, 2, 0, 0, 1}, B[6] = {0, 1, 2, 1, 2, 2};
     const int rep = (threadIdx.x & 63) & (NMREP - 1);
     for (uint32_t k = threadIdx.x; k < n; k += 256) {
-        const int x = min(max((int)floor((double)c[0][k]), 0), d.nx - 1);
-        const int y = min(max((int)floor((double)c[1][k]), d.ylo), d.yhi - 1);
-        const int z = min(max((int)floor((double)c[2][k]), 0), d.nz - 1);
-        const double v[3] = {(double)c[3][k], (double)c[4][k], (double)c[5][k]};
+        PT px[3], pv[3];
+        uint32_t id;
+        load_part<3, PT>(P, d.slot_off + (long long)T * d.cap, k, px, pv, id);
+        const int x = min(max((int)floor((double)px[0]), 0), d.nx - 1);
+        const int y = min(max((int)floor((double)px[1]), d.ylo), d.yhi - 1);
+        const int z = min(max((int)floor((double)px[2]), 0), d.nz - 1);
+        const double v[3] = {(double)pv[0], (double)pv[1], (double)pv[2]};
         double m[10];
         m[0] = 1.0;
         for (int a = 0; a < 3; ++a) m[1 + a] = v[a];
@@ -1107,14 +1108,14 @@ __global__ void __launch_bounds__(256) k_node_moments(const InstDesc* __restrict
     }
 }
 
-hipError_t closure_node_moments(int part_fp, const InstDesc* D, int inst, long long ntiles, const void* pos0,
-                                long long cstride, const uint32_t* fill, double* nm, hipStream_t s) {
+hipError_t closure_node_moments(int part_fp, const InstDesc* D, int inst, long long ntiles, const PartBuf& buf,
+                                const uint32_t* fill, double* nm, hipStream_t s) {
     if (part_fp == 64)
         hipLaunchKernelGGL(k_node_moments<double>, dim3((unsigned)ntiles), dim3(256), 0, s, D, inst,
-                           (const unsigned char*)pos0, cstride, fill, nm);
+                           buf, fill, nm);
     else
         hipLaunchKernelGGL(k_node_moments<float>, dim3((unsigned)ntiles), dim3(256), 0, s, D, inst,
-                           (const unsigned char*)pos0, cstride, fill, nm);
+                           buf, fill, nm);
     return hipGetLastError();
 }
 

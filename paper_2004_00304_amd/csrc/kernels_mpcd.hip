@@ -5,8 +5,6 @@
 
 namespace lbmpcd {
 
-size_t particle_lds_bytes(int, int, int) { return LDS_HDR + LDS_UNI; }
-
 namespace {
 struct PlainModes {
     template <int DIM, typename PT, int NT, int PPT, int OVF = 0>

@@ -18,7 +18,7 @@ __device__ __forceinline__ double poiseuille_p(const InstDesc& d, double gk, dou
 
 template <int DIM, typename PT>
 __global__ void __launch_bounds__(WG) k_part_init(const InstDesc* __restrict__ D, int n_inst, long long total,
-                                                  PartPtrs<PT> P) {
+                                                  PStore<DIM, PT> P) {
     long long gid = (long long)blockIdx.x * WG + threadIdx.x;
     if (gid >= total) return;
     int ii = find_inst(D, n_inst, gid, [](const InstDesc& d) { return d.part_off; });
@@ -43,14 +43,14 @@ __global__ void __launch_bounds__(WG) k_part_init(const InstDesc* __restrict__ D
     const long long lcell = (I - tx * d.Tx) + (long long)cx * ((J - ty * d.Ty) + (long long)cy * (K - tz * d.Tz));
     const long long slot = lcell * d.ppc + id % d.ppc;
     const long long g = d.slot_off + tile * d.cap + slot;
-    P.id[g] = (uint32_t)id;
-    P.pos[0][g] = (PT)x;
-    P.pos[1][g] = (PT)y;
-    if (DIM == 3) P.pos[2][g] = (PT)zz;
+    *P.id(g) = (uint32_t)id;
+    *P.pos(0, g) = (PT)x;
+    *P.pos(1, g) = (PT)y;
+    if (DIM == 3) *P.pos(2, g) = (PT)zz;
 #pragma unroll
     for (int q = 0; q < DIM; ++q) {
         const double u0 = d.init_flow ? poiseuille_p(d, d.g[q], y) : 0.0;
-        P.vel[q][g] = (PT)(u0 + d.sd * z[q]);
+        *P.vel(q, g) = (PT)(u0 + d.sd * z[q]);
     }
 }
 
@@ -69,46 +69,84 @@ __global__ void __launch_bounds__(WG) k_fill_sequential(const InstDesc* __restri
     other[T] = 0u;
 }
 
-// Particles of one instance in id order (and their cell in the binning of
-// (t, sub)).
-template <int DIM, typename PT>
-__global__ void __launch_bounds__(WG) k_gather(const InstDesc* __restrict__ D, int inst, PartPtrs<PT> P,
-                                               const uint32_t* __restrict__ fill, double* pos_out,
-                                               double* vel_out, int* cell_out, long long t, int sub) {
+// Item of workgroup b of xcd_grid(items): the workgroups the hardware deals to
+// one XCD take one contiguous range, so that what neighbouring items scatter
+// to (or gather from) the same cache lines meets in one L2.
+__device__ __forceinline__ long long xcd_item() {
+    return (long long)(blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
+}
+static inline unsigned xcd_grid(long long items) { return (unsigned)(8 * ((items + 7) / 8)); }
+
+enum GatherWhat { GATHER_POS, GATHER_VEL, GATHER_CELL, GATHER_INV };
+
+// Positions, velocities or cells (in the binning of (t, sub)) of one
+// instance's particles scattered to their ids, or (GATHER_INV) the slots of
+// the ids; one workgroup per tile.
+template <int DIM, typename PT, int WHAT>
+__global__ void __launch_bounds__(WG) k_scatter(const InstDesc* __restrict__ D, int inst, PartBuf P,
+                                                const uint32_t* __restrict__ fill, double* out, int* out32, long long t,
+                                                int sub) {
     const InstDesc& d = D[inst];
-    const long long s = (long long)blockIdx.x * WG + threadIdx.x;
-    if (s >= d.ntiles * d.cap) return;
-    const long long lt = s / d.cap;
-    const int k = (int)(s % d.cap);
-    uint32_t n = fill[d.tile_off + lt];
-    if (n > (uint32_t)d.cap) n = (uint32_t)d.cap;
-    if ((uint32_t)k >= n) return;
-    const long long g = d.slot_off + s;
-    const uint32_t id = P.id[g];
-    if ((long long)id >= d.Np) return;
+    // eight-byte components of a tile's surroundings overflow one L2: tiles
+    // in order, so that the XCDs share them in the cache behind it
+    const long long lt = WHAT == GATHER_INV ? xcd_item() : (long long)blockIdx.x;
+    if (lt >= d.ntiles) return;
+    const uint32_t n = min(fill[d.tile_off + lt], (uint32_t)d.cap);
+    const long long base = d.slot_off + lt * d.cap;
+    PT sh[3];
+    if constexpr (WHAT == GATHER_CELL) grid_shift_of<DIM, PT>(d, (uint32_t)t, (uint32_t)sub, sh);
+    for (uint32_t k = threadIdx.x; k < n; k += WG) {
+        PT px[3], pv[3];
+        uint32_t id;
+        load_part<DIM, PT>(P, base, k, px, pv, id);
+        if constexpr (PStore<DIM, PT>::ID_APART) id = load_id<DIM, PT>(P, base, k);
+        if ((long long)id >= d.Np) continue;
+        if constexpr (WHAT == GATHER_INV) {
+            out32[id] = (int)(lt * d.cap + k);
+        } else if constexpr (WHAT == GATHER_CELL) {
+            const PT rr = (PT)d.r;
+            int ix = bin_coord<PT>(px[0], (PT)0, sh[0], rr);
+            if (ix >= d.Cx) ix -= d.Cx;
+            const int iy = bin_row<PT>(d, px[1], sh[1], rr);
+            int iz = 0;
+            if (DIM == 3) {
+                iz = bin_coord<PT>(px[2], (PT)0, sh[2], rr);
+                if (iz >= d.Cz) iz -= d.Cz;
+            }
+            out32[id] = ix + d.Cx * (iy + d.CyB * iz);
+        } else {
 #pragma unroll
-    for (int q = 0; q < DIM; ++q) {
-        if (pos_out) pos_out[(long long)q * d.Np + id] = (double)P.pos[q][g];
-        if (vel_out) vel_out[(long long)q * d.Np + id] = (double)P.vel[q][g];
-    }
-    if (cell_out) {
-        PT sh[3];
-        grid_shift_of<DIM, PT>(d, (uint32_t)t, (uint32_t)sub, sh);
-        const PT rr = (PT)d.r;
-        int ix = bin_coord<PT>(P.pos[0][g], (PT)0, sh[0], rr);
-        if (ix >= d.Cx) ix -= d.Cx;
-        const int iy = bin_row<PT>(d, P.pos[1][g], sh[1], rr);
-        int iz = 0;
-        if (DIM == 3) {
-            iz = bin_coord<PT>(P.pos[2][g], (PT)0, sh[2], rr);
-            if (iz >= d.Cz) iz -= d.Cz;
+            for (int q = 0; q < DIM; ++q) out[(long long)q * d.Np + id] = (double)(WHAT == GATHER_POS ? px[q] : pv[q]);
         }
-        cell_out[id] = ix + d.Cx * (iy + d.CyB * iz);
     }
 }
 
+// Positions or velocities in id order through the slots of the ids: one thread
+// per id, the stores consecutive.
+template <int DIM, typename PT, int WHAT>
+__global__ void __launch_bounds__(WG) k_gather(const InstDesc* __restrict__ D, int inst, PartBuf P,
+                                               const uint32_t* __restrict__ slot, double* out) {
+    const InstDesc& d = D[inst];
+    const long long id = (long long)blockIdx.x * WG + threadIdx.x;
+    if (id >= d.Np) return;
+    const long long s = slot[id];
+    if (s >= d.ntiles * d.cap) return;  // a particle lost to an overflow
+    PT px[3], pv[3];
+    const PStore<DIM, PT> S{P.b, P.cs};
+    const long long g = d.slot_off + s;
+    if constexpr (S.F32 && WHAT == GATHER_POS) {
+        const u32x4 a = *(const u32x4*)S.pos(0, g);
+        px[0] = as_f(a.x); px[1] = as_f(a.y); px[2] = as_f(a.z);
+    } else {
+#pragma unroll
+        for (int q = 0; q < DIM; ++q) (WHAT == GATHER_POS ? px : pv)[q] = WHAT == GATHER_POS ? *S.pos(q, g) : *S.vel(q, g);
+    }
+#pragma unroll
+    for (int q = 0; q < DIM; ++q) out[(long long)q * d.Np + id] = (double)(WHAT == GATHER_POS ? px[q] : pv[q]);
+}
+
 template <int DIM, typename PT>
-__global__ void __launch_bounds__(WG) k_cell_count(const InstDesc* __restrict__ D, int inst, PartPtrs<PT> P,
+__global__ void __launch_bounds__(WG) k_cell_count(const InstDesc* __restrict__ D, int inst, PStore<DIM, PT> P,
                                                    const uint32_t* __restrict__ fill, int* count, long long t,
                                                    int sub) {
     const InstDesc& d = D[inst];
@@ -123,12 +161,12 @@ __global__ void __launch_bounds__(WG) k_cell_count(const InstDesc* __restrict__ 
     PT sh[3];
     grid_shift_of<DIM, PT>(d, (uint32_t)t, (uint32_t)sub, sh);
     const PT rr = (PT)d.r;
-    int ix = bin_coord<PT>(P.pos[0][g], (PT)0, sh[0], rr);
+    int ix = bin_coord<PT>(*P.pos(0, g), (PT)0, sh[0], rr);
     if (ix >= d.Cx) ix -= d.Cx;
-    const int iy = bin_row<PT>(d, P.pos[1][g], sh[1], rr);
+    const int iy = bin_row<PT>(d, *P.pos(1, g), sh[1], rr);
     int iz = 0;
     if (DIM == 3) {
-        iz = bin_coord<PT>(P.pos[2][g], (PT)0, sh[2], rr);
+        iz = bin_coord<PT>(*P.pos(2, g), (PT)0, sh[2], rr);
         if (iz >= d.Cz) iz -= d.Cz;
     }
     atomicAdd(&count[ix + d.Cx * (iy + d.CyB * iz)], 1);
@@ -136,24 +174,18 @@ __global__ void __launch_bounds__(WG) k_cell_count(const InstDesc* __restrict__ 
 
 // Overwrite positions (which = 0) or velocities (1) of one instance by id.
 template <int DIM, typename PT>
-__global__ void __launch_bounds__(WG) k_set_field(const InstDesc* __restrict__ D, int inst, PartPtrs<PT> P,
+__global__ void __launch_bounds__(WG) k_set_field(const InstDesc* __restrict__ D, int inst, PStore<DIM, PT> P,
                                                   const uint32_t* __restrict__ fill, int which,
                                                   const double* __restrict__ src) {
     const InstDesc& d = D[inst];
-    const long long s = (long long)blockIdx.x * WG + threadIdx.x;
-    if (s >= d.ntiles * d.cap) return;
-    const long long lt = s / d.cap;
-    const int k = (int)(s % d.cap);
-    uint32_t n = fill[d.tile_off + lt];
-    if (n > (uint32_t)d.cap) n = (uint32_t)d.cap;
-    if ((uint32_t)k >= n) return;
-    const long long g = d.slot_off + s;
-    const uint32_t id = P.id[g];
-    if ((long long)id >= d.Np) return;
+    const long long lt = blockIdx.x;
+    const uint32_t n = min(fill[d.tile_off + lt], (uint32_t)d.cap);
+    for (uint32_t k = threadIdx.x; k < n; k += WG) {
+        const long long g = d.slot_off + lt * d.cap + k;
+        const uint32_t id = *P.id(g);
+        if ((long long)id >= d.Np) continue;
 #pragma unroll
-    for (int q = 0; q < DIM; ++q) {
-        const PT v = (PT)src[(long long)q * d.Np + id];
-        if (which == 0) P.pos[q][g] = v; else P.vel[q][g] = v;
+        for (int q = 0; q < DIM; ++q) *(which == 0 ? P.pos(q, g) : P.vel(q, g)) = (PT)src[(long long)q * d.Np + id];
     }
 }
 
@@ -187,10 +219,10 @@ hipError_t launch_part_init(int dim, int part_fp, const InstDesc* D, int n_inst,
                             hipStream_t s) {
     if (total <= 0) return hipSuccess;
     dim3 g(nblk(total)), b(WG);
-    if (dim == 2 && part_fp == 64) hipLaunchKernelGGL((k_part_init<2, double>), g, b, 0, s, D, n_inst, total, typed<double>(buf));
-    else if (dim == 2) hipLaunchKernelGGL((k_part_init<2, float>), g, b, 0, s, D, n_inst, total, typed<float>(buf));
-    else if (part_fp == 64) hipLaunchKernelGGL((k_part_init<3, double>), g, b, 0, s, D, n_inst, total, typed<double>(buf));
-    else hipLaunchKernelGGL((k_part_init<3, float>), g, b, 0, s, D, n_inst, total, typed<float>(buf));
+    if (dim == 2 && part_fp == 64) hipLaunchKernelGGL((k_part_init<2, double>), g, b, 0, s, D, n_inst, total, typed<2, double>(buf));
+    else if (dim == 2) hipLaunchKernelGGL((k_part_init<2, float>), g, b, 0, s, D, n_inst, total, typed<2, float>(buf));
+    else if (part_fp == 64) hipLaunchKernelGGL((k_part_init<3, double>), g, b, 0, s, D, n_inst, total, typed<3, double>(buf));
+    else hipLaunchKernelGGL((k_part_init<3, float>), g, b, 0, s, D, n_inst, total, typed<3, float>(buf));
     return hipGetLastError();
 }
 
@@ -201,15 +233,44 @@ hipError_t launch_fill_sequential(const InstDesc* D, int n_inst, long long tiles
     return hipGetLastError();
 }
 
-hipError_t launch_gather(int dim, int part_fp, const InstDesc* D, int inst, PartBuf buf, const uint32_t* fill,
-                         double* pos_out, double* vel_out, int* cell_out, long long slots, long long t, int sub,
-                         hipStream_t s) {
-    if (slots <= 0) return hipSuccess;
-    dim3 g(nblk(slots)), b(WG);
-    if (dim == 2 && part_fp == 64) hipLaunchKernelGGL((k_gather<2, double>), g, b, 0, s, D, inst, typed<double>(buf), fill, pos_out, vel_out, cell_out, t, sub);
-    else if (dim == 2) hipLaunchKernelGGL((k_gather<2, float>), g, b, 0, s, D, inst, typed<float>(buf), fill, pos_out, vel_out, cell_out, t, sub);
-    else if (part_fp == 64) hipLaunchKernelGGL((k_gather<3, double>), g, b, 0, s, D, inst, typed<double>(buf), fill, pos_out, vel_out, cell_out, t, sub);
-    else hipLaunchKernelGGL((k_gather<3, float>), g, b, 0, s, D, inst, typed<float>(buf), fill, pos_out, vel_out, cell_out, t, sub);
+// From this many particles on, positions and velocities go through the inverse
+// map (in `idle`, memory of at least 4 bytes a particle): one scattered 4-byte
+// store a particle, then consecutive 8-byte stores, instead of a scattered
+// 8-byte store for every component.  A tile's ids come from all its
+// surroundings, the more so the longer the run.  Binary32 records, which one
+// or two loads fetch, us a field directly / through the map after 100 LB
+// steps: 0.66M particles 30 / 25, 10.5M 487 / 461, 41.9M 3303 / 1736 (1535 /
+// 1213 after 2 LB steps).  Binary64 in 3D takes two loads a field from arrays
+// of their own: 10.5M 498 / 656, 21M 1621 / 1305.
+template <typename PT>
+constexpr long long gather_inv_min() { return sizeof(PT) == 4 ? 1 << 18 : 1 << 24; }
+
+template <int DIM, typename PT>
+static void gather(const InstDesc* D, int inst, const InstDesc& d, PartBuf buf, const uint32_t* fill, double* pos_out,
+                   double* vel_out, int* cell_out, void* idle, long long t, int sub, hipStream_t s) {
+    const dim3 b(WG), tiles((unsigned)d.ntiles);
+    if (cell_out) {
+        hipLaunchKernelGGL((k_scatter<DIM, PT, GATHER_CELL>), tiles, b, 0, s, D, inst, buf, fill, nullptr, cell_out, t, sub);
+    } else if (d.Np < gather_inv_min<PT>()) {
+        if (pos_out) hipLaunchKernelGGL((k_scatter<DIM, PT, GATHER_POS>), tiles, b, 0, s, D, inst, buf, fill, pos_out, nullptr, t, sub);
+        else hipLaunchKernelGGL((k_scatter<DIM, PT, GATHER_VEL>), tiles, b, 0, s, D, inst, buf, fill, vel_out, nullptr, t, sub);
+    } else {
+        const dim3 ids(nblk(d.Np));
+        const uint32_t* slot = (const uint32_t*)idle;
+        hipLaunchKernelGGL((k_scatter<DIM, PT, GATHER_INV>), dim3(xcd_grid(d.ntiles)), b, 0, s, D, inst, buf, fill, nullptr, (int*)idle, t, sub);
+        if (pos_out) hipLaunchKernelGGL((k_gather<DIM, PT, GATHER_POS>), ids, b, 0, s, D, inst, buf, slot, pos_out);
+        else hipLaunchKernelGGL((k_gather<DIM, PT, GATHER_VEL>), ids, b, 0, s, D, inst, buf, slot, vel_out);
+    }
+}
+
+hipError_t launch_gather(int dim, int part_fp, const InstDesc* D, int inst, const InstDesc& d, PartBuf buf,
+                         const uint32_t* fill, double* pos_out, double* vel_out, int* cell_out, void* idle, long long t,
+                         int sub, hipStream_t s) {
+    if (d.ntiles <= 0) return hipSuccess;
+    if (dim == 2 && part_fp == 64) gather<2, double>(D, inst, d, buf, fill, pos_out, vel_out, cell_out, idle, t, sub, s);
+    else if (dim == 2) gather<2, float>(D, inst, d, buf, fill, pos_out, vel_out, cell_out, idle, t, sub, s);
+    else if (part_fp == 64) gather<3, double>(D, inst, d, buf, fill, pos_out, vel_out, cell_out, idle, t, sub, s);
+    else gather<3, float>(D, inst, d, buf, fill, pos_out, vel_out, cell_out, idle, t, sub, s);
     return hipGetLastError();
 }
 
@@ -217,21 +278,21 @@ hipError_t launch_cell_count(int dim, int part_fp, const InstDesc* D, int inst, 
                              int* count_out, long long slots, long long t, int sub, hipStream_t s) {
     if (slots <= 0) return hipSuccess;
     dim3 g(nblk(slots)), b(WG);
-    if (dim == 2 && part_fp == 64) hipLaunchKernelGGL((k_cell_count<2, double>), g, b, 0, s, D, inst, typed<double>(buf), fill, count_out, t, sub);
-    else if (dim == 2) hipLaunchKernelGGL((k_cell_count<2, float>), g, b, 0, s, D, inst, typed<float>(buf), fill, count_out, t, sub);
-    else if (part_fp == 64) hipLaunchKernelGGL((k_cell_count<3, double>), g, b, 0, s, D, inst, typed<double>(buf), fill, count_out, t, sub);
-    else hipLaunchKernelGGL((k_cell_count<3, float>), g, b, 0, s, D, inst, typed<float>(buf), fill, count_out, t, sub);
+    if (dim == 2 && part_fp == 64) hipLaunchKernelGGL((k_cell_count<2, double>), g, b, 0, s, D, inst, typed<2, double>(buf), fill, count_out, t, sub);
+    else if (dim == 2) hipLaunchKernelGGL((k_cell_count<2, float>), g, b, 0, s, D, inst, typed<2, float>(buf), fill, count_out, t, sub);
+    else if (part_fp == 64) hipLaunchKernelGGL((k_cell_count<3, double>), g, b, 0, s, D, inst, typed<3, double>(buf), fill, count_out, t, sub);
+    else hipLaunchKernelGGL((k_cell_count<3, float>), g, b, 0, s, D, inst, typed<3, float>(buf), fill, count_out, t, sub);
     return hipGetLastError();
 }
 
 hipError_t launch_set_field(int dim, int part_fp, const InstDesc* D, int inst, PartBuf buf, const uint32_t* fill,
-                            int which, const double* src, long long slots, hipStream_t s) {
-    if (slots <= 0) return hipSuccess;
-    dim3 g(nblk(slots)), b(WG);
-    if (dim == 2 && part_fp == 64) hipLaunchKernelGGL((k_set_field<2, double>), g, b, 0, s, D, inst, typed<double>(buf), fill, which, src);
-    else if (dim == 2) hipLaunchKernelGGL((k_set_field<2, float>), g, b, 0, s, D, inst, typed<float>(buf), fill, which, src);
-    else if (part_fp == 64) hipLaunchKernelGGL((k_set_field<3, double>), g, b, 0, s, D, inst, typed<double>(buf), fill, which, src);
-    else hipLaunchKernelGGL((k_set_field<3, float>), g, b, 0, s, D, inst, typed<float>(buf), fill, which, src);
+                            int which, const double* src, long long ntiles, hipStream_t s) {
+    if (ntiles <= 0) return hipSuccess;
+    dim3 g((unsigned)ntiles), b(WG);
+    if (dim == 2 && part_fp == 64) hipLaunchKernelGGL((k_set_field<2, double>), g, b, 0, s, D, inst, typed<2, double>(buf), fill, which, src);
+    else if (dim == 2) hipLaunchKernelGGL((k_set_field<2, float>), g, b, 0, s, D, inst, typed<2, float>(buf), fill, which, src);
+    else if (part_fp == 64) hipLaunchKernelGGL((k_set_field<3, double>), g, b, 0, s, D, inst, typed<3, double>(buf), fill, which, src);
+    else hipLaunchKernelGGL((k_set_field<3, float>), g, b, 0, s, D, inst, typed<3, float>(buf), fill, which, src);
     return hipGetLastError();
 }
 

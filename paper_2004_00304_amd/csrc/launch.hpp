@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include "common.hpp"
+#include "pstore.hpp"
 
 namespace lbmpcd {
 
@@ -24,21 +25,6 @@ hipError_t launch_lb_init(int dim, int lb_fp, const InstDesc* D, int n_inst, lon
                           double* fbu, long long fb_stride, hipStream_t s);
 hipError_t launch_moments(int dim, int lb_fp, const InstDesc* D, int inst, long long N, const void* f,
                           double* rho, double* u, double* pi, hipStream_t s);
-
-// Buffers of one particle store, type-erased (positions, velocities, ids).
-struct PartBuf {
-    void* pos[3];
-    void* vel[3];
-    uint32_t* id;
-};
-
-template <typename PT>
-inline PartPtrs<PT> typed(const PartBuf& b) {
-    PartPtrs<PT> p;
-    for (int q = 0; q < 3; ++q) { p.pos[q] = (PT*)b.pos[q]; p.vel[q] = (PT*)b.vel[q]; }
-    p.id = b.id;
-    return p;
-}
 
 struct ParticleLaunch {
     int dim, part_fp, mode;       // mode bit 0: collide, bit 1: stream, bit 2: MPCD-AT instead of SRD,
@@ -65,28 +51,28 @@ struct ParticleLaunch {
     int cap_max;                  // largest tile capacity
     int wg_threads;               // 256 or 512 threads per workgroup (0: 256)
     int xcd_blocked;              // 1: each XCD's workgroups take a contiguous range of tiles
-    long long cstride;            // bytes between component arrays (pos[k] = pos[0] + k cstride, vel[k] = pos[0] + (dim + k) cstride, id after vel)
-    size_t lds_bytes;
     uint32_t* ovf;                // [2 + tiles] overflow list of a two-pass launch (zero-initialised), or
                                   // null: the context does not take the two-pass form
     int exp_max;                  // largest expected tile occupancy (particles per cell x cells per tile)
 };
 
 hipError_t launch_particles(const ParticleLaunch& L, hipStream_t s);
-size_t particle_lds_bytes(int dim, int part_fp, int cap);
 
 hipError_t launch_part_init(int dim, int part_fp, const InstDesc* D, int n_inst, long long total_particles,
                             PartBuf buf, hipStream_t s);
 hipError_t launch_fill_sequential(const InstDesc* D, int n_inst, long long tiles, uint32_t* fill,
                                   uint32_t* fill_other, hipStream_t s);
-// Per-instance kernels cover `slots` = ntiles * cap of that instance.
-hipError_t launch_gather(int dim, int part_fp, const InstDesc* D, int inst, PartBuf buf, const uint32_t* fill,
-                         double* pos_out, double* vel_out, int* cell_out, long long slots, long long t, int sub,
-                         hipStream_t s);
+// Particle state of one instance (d: its descriptor on the host) by id: one of
+// pos_out, vel_out ([dim][Np]) and cell_out.  idle: the particle buffer not in
+// use, overwritten.
+hipError_t launch_gather(int dim, int part_fp, const InstDesc* D, int inst, const InstDesc& d, PartBuf buf,
+                         const uint32_t* fill, double* pos_out, double* vel_out, int* cell_out, void* idle, long long t,
+                         int sub, hipStream_t s);
+// Covers `slots` = ntiles * cap of that instance.
 hipError_t launch_cell_count(int dim, int part_fp, const InstDesc* D, int inst, PartBuf buf, const uint32_t* fill,
                              int* count_out, long long slots, long long t, int sub, hipStream_t s);
 hipError_t launch_set_field(int dim, int part_fp, const InstDesc* D, int inst, PartBuf buf, const uint32_t* fill,
-                            int which, const double* src, long long slots, hipStream_t s);
+                            int which, const double* src, long long ntiles, hipStream_t s);
 hipError_t launch_zero(void* p, size_t bytes, hipStream_t s);
 hipError_t launch_exclusive_scan(int* a, long long n, hipStream_t s);
 hipError_t launch_node_mean(const double* acc, long long nslab, int dim, int det, double* out, hipStream_t s);

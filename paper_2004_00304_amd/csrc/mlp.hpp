@@ -5,6 +5,7 @@
 #include <cstdint>
 
 #include "common.hpp"
+#include "launch.hpp"
 
 namespace lbmpcd {
 
@@ -118,8 +119,8 @@ hipError_t mlp_destandardize_uc(const float* Y, const float* stats, const float*
                                 hipStream_t s);
 // Particle moments per slab node (count, sum v, sum v v) of one channel;
 // one workgroup per particle tile.
-hipError_t closure_node_moments(int part_fp, const InstDesc* D, int inst, long long ntiles, const void* pos0,
-                                long long cstride, const uint32_t* fill, double* nm, hipStream_t s);
+hipError_t closure_node_moments(int part_fp, const InstDesc* D, int inst, long long ntiles, const PartBuf& buf,
+                                const uint32_t* fill, double* nm, hipStream_t s);
 // Averages of a collection window of K LB steps: features X [nslab][NF] and
 // targets Y [nslab][NOUT] (mean velocity, kinetic stress per unit volume).
 hipError_t closure_collect_finish(long long nslab, int K, double mass, const double* facc, const double* nm,

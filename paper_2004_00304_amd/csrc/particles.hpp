@@ -2,8 +2,8 @@
 // kernels_mpcd.hip, kernels_mpcd_ce.hip and kernels_mpcd_det.hip instantiate it).
 //
 // Particle layout.  The cells of the shifted grid are grouped into tiles of
-// Tx x Ty x Tz cells; every tile owns `cap` slots in each SoA component
-// array (x, y, z, vx, vy, vz, id).  After the binning of an MPCD step every
+// Tx x Ty x Tz cells; every tile owns `cap` slots of the particle buffer
+// (PStore).  After the binning of an MPCD step every
 // particle sits in the slots of the tile that contains its cell, in no
 // particular order inside the tile.
 //
@@ -21,10 +21,10 @@
 //     boundary conditions, samples of the last MPCD step of an LB step,
 //     binning into the new shifted grid;
 //   phase 3 (counting sort into tiles): each wave groups its particles by
-//     destination tile with ballots; the first lane of a group claims a row
-//     of a small LDS table of destination tiles; one global atomic per
-//     destination reserves a run of slots, and every store writes the lanes
-//     of a group to consecutive slots.
+//     destination tile; the first lane of a group claims a row of a small LDS
+//     table of destination tiles; one global atomic per destination reserves a
+//     run of slots, and every store writes the lanes of a group to consecutive
+//     slots.
 // Every particle is read once and written once per MPCD step.
 #pragma once
 
@@ -35,20 +35,10 @@
 
 namespace lbmpcd {
 
-// Particle buffers are passed as one base pointer each: component k of
-// x, y, (z), vx, vy, (vz) at base + k * cs bytes, the ids after the last one.
-template <typename PT>
-struct PBuf {
-    unsigned char* b;
-    __device__ __forceinline__ PT* comp(int k, long long cs) const { return (PT*)(b + k * cs); }
-    __device__ __forceinline__ uint32_t* id(int dim, long long cs) const { return (uint32_t*)(b + 2 * dim * cs); }
-};
-
 template <typename PT>
 struct PArgs {
     const InstDesc* D;
-    PBuf<PT> in, out;
-    long long cs;
+    PartBuf in, out;
     uint32_t* fill_in;
     uint32_t* fill_out;
     const int* tile_inst;
@@ -70,28 +60,6 @@ struct PArgs {
     uint32_t* ovf;
     int ovf_mode;
 };
-
-// Binary32 particle arrays are read and written with buffer instructions:
-// one resource per component array (its uniform 64-bit base in scalar
-// registers) and a 32-bit byte offset per lane, so that no lane computes a
-// 64-bit address (a channel's slots span less than 4 GiB per component).
-// Binary64 particles keep global loads and stores, measured 1 % faster.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t comp_rsrc(const unsigned char* p) {
-    return __builtin_amdgcn_make_buffer_rsrc((void*)p, (short)0, -1, 0x00020000);
-}
-template <typename PT>
-__device__ __forceinline__ PT buf_load(__amdgpu_buffer_rsrc_t r, uint32_t off) {
-    if constexpr (sizeof(PT) == 4) return __builtin_bit_cast(PT, __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
-    else return __builtin_bit_cast(PT, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0));
-}
-template <typename PT>
-__device__ __forceinline__ void buf_store(__amdgpu_buffer_rsrc_t r, uint32_t off, PT v) {
-    if constexpr (sizeof(PT) == 4) __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, (int)off, 0, 0);
-    else {
-        typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, (int)off, 0, 0);
-    }
-}
 
 template <typename PT>
 __device__ __forceinline__ PT wrap_periodic(PT x, PT lo, PT L) {
@@ -297,7 +265,6 @@ __device__ __forceinline__ void particle_tile(const PArgs<PT>& A, long long T, u
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const long long cs = A.cs;
     const int ii = cptr(A.tile_inst)[T];
     cst<InstDesc>& d = cptr(A.D)[ii];
     const Key key = key_of(d);
@@ -318,10 +285,6 @@ __device__ __forceinline__ void particle_tile(const PArgs<PT>& A, long long T, u
     const int tx = (int)(rem - tyu * (uint32_t)d.ntx), ty = (int)tyu, tz = (int)tzu;
     const int cap = d.cap;
     const long long base = d.slot_off + (long long)lt * cap;
-    // A channel's slots span less than 4 GiB per component, so every particle
-    // access is a uniform 64-bit base plus a 32-bit lane offset.
-    const unsigned char* tin = A.in.b + base * (long long)sizeof(PT);
-    const unsigned char* tin_id = A.in.b + 2 * DIM * cs + base * 4;
     uint32_t n = cptr(A.fill_in)[T];
     if (A.ovf_mode == 1 && n > (uint32_t)(NT * PPT)) {
         // more particles than this launch's slots: left untouched for the
@@ -341,32 +304,25 @@ __device__ __forceinline__ void particle_tile(const PArgs<PT>& A, long long T, u
     uint32_t pid[PPT];
     PT px[PPT][3], pv[PPT][3];
     bool valid[PPT];
-#pragma unroll
-    for (int k = 0; k < PPT; ++k) {
+    // What would be spilled as it arrives is loaded later, since each such
+    // load waits for the one before it: an id in an array of its own, needed
+    // first by the draws after an SRD collision, is loaded there (binary64
+    // ensemble 2.53 -> 2.10 ms per MPCD step), and of six binary32 records
+    // the last comes after the rotations are drawn, whose FP64 series need the
+    // registers (95 VGPRs and 16 spilled bytes -> 89 and none; film 5.51 ->
+    // 5.38 ms).  MPCD-AT and the Chapman-Enskog modes do not spill there.
+    constexpr bool ID_LATE = PStore<DIM, PT>::ID_APART && !AT;
+    constexpr int FIRST = (PPT == 6 && sizeof(PT) == 4 && !AT && !CE) ? PPT - 1 : PPT;
+    auto load = [&](int k) {
         const int s = tid + k * NT;
         valid[k] = s < (int)n;
+        // (an absent particle's registers are never read)
+        if (!valid[k]) return;
+        load_part<DIM, PT>(A.in, base, (uint32_t)s, px[k], pv[k], pid[k]);
+        if constexpr (PStore<DIM, PT>::ID_APART && !ID_LATE) pid[k] = load_id<DIM, PT>(A.in, base, (uint32_t)s);
+    };
 #pragma unroll
-        for (int c = 0; c < 3; ++c) { px[k][c] = (PT)0; pv[k][c] = (PT)0; }
-        pid[k] = 0;
-        if (valid[k]) {
-            const uint32_t o = (uint32_t)s * (uint32_t)sizeof(PT);
-            if constexpr (sizeof(PT) == 4) {
-                pid[k] = buf_load<uint32_t>(comp_rsrc(tin_id), (uint32_t)s * 4u);
-#pragma unroll
-                for (int c = 0; c < DIM; ++c) {
-                    px[k][c] = buf_load<PT>(comp_rsrc(tin + c * cs), o);
-                    pv[k][c] = buf_load<PT>(comp_rsrc(tin + (DIM + c) * cs), o);
-                }
-            } else {
-                pid[k] = *(const uint32_t*)(tin_id + (uint32_t)s * 4u);
-#pragma unroll
-                for (int c = 0; c < DIM; ++c) {
-                    px[k][c] = *(const PT*)(tin + c * cs + o);
-                    pv[k][c] = *(const PT*)(tin + (DIM + c) * cs + o);
-                }
-            }
-        }
-    }
+    for (int k = 0; k < FIRST; ++k) load(k);
     if (tid == 0 && n > (uint32_t)(3 * cap / 4)) atomicMax(&A.stats->max_fill, n);
     if (tid < 4) wstat[tid] = 0u;
     if constexpr (STREAM) {
@@ -422,8 +378,10 @@ __device__ __forceinline__ void particle_tile(const PArgs<PT>& A, long long T, u
             ccnt[j] = 0u;
             csv[3 * j] = 0.0; csv[3 * j + 1] = 0.0; csv[3 * j + 2] = 0.0;
         }
-        __syncthreads();
     }
+#pragma unroll
+    for (int k = FIRST; k < PPT; ++k) load(k);
+    if constexpr (COLL) __syncthreads();
 
     // ---- phase 1: collision (SRD, or MPCD-AT) of the binning these particles sit in
     if constexpr (COLL) {
@@ -546,13 +504,12 @@ __device__ __forceinline__ void particle_tile(const PArgs<PT>& A, long long T, u
         }
         if constexpr (!STREAM) {
             // collision only: velocities go back to their slots
-            unsigned char* tout = A.out.b + base * (long long)sizeof(PT);
+            const PStore<DIM, PT> out{A.out.b, A.out.cs};
 #pragma unroll
             for (int k = 0; k < PPT; ++k) {
                 if (!valid[k]) continue;
-                const uint32_t o = (uint32_t)(tid + k * NT) * (uint32_t)sizeof(PT);
 #pragma unroll
-                for (int q = 0; q < DIM; ++q) *(PT*)(tout + (DIM + q) * cs + o) = pv[k][q];
+                for (int q = 0; q < DIM; ++q) *out.vel(q, base + tid + k * NT) = pv[k][q];
             }
             if (tid == 0 && wstat[1]) atomicAdd(&A.stats->misplaced, (unsigned long long)wstat[1]);
             return;
@@ -560,6 +517,11 @@ __device__ __forceinline__ void particle_tile(const PArgs<PT>& A, long long T, u
     }
 
     if constexpr (STREAM) {
+        if constexpr (ID_LATE) {
+#pragma unroll
+            for (int k = 0; k < PPT; ++k)
+                if (valid[k]) pid[k] = load_id<DIM, PT>(A.in, base, (uint32_t)(tid + k * NT));
+        }
         const uint32_t ts = (uint32_t)t_now;
         const uint32_t ss = (uint32_t)A.str_s;
         cst<double>* shs = shtab + ((t_now & 1) * d.S + ss) * 3;
@@ -881,8 +843,6 @@ __device__ __forceinline__ void particle_tile(const PArgs<PT>& A, long long T, u
             gbase[tid] = c > 0u ? atomicAdd(&A.fill_out[d.tile_off + hkey[tid]], c) : 0u;
         }
         __syncthreads();
-        unsigned char* och = A.out.b + d.slot_off * (long long)sizeof(PT);
-        unsigned char* och_id = A.out.b + 2 * DIM * cs + d.slot_off * 4;
 #pragma unroll
         for (int k = 0; k < PPT; ++k) {
             const uint32_t e = pk[k];
@@ -901,22 +861,7 @@ __device__ __forceinline__ void particle_tile(const PArgs<PT>& A, long long T, u
                 atomicAdd(&A.stats->dropped, 1ull);
                 continue;
             }
-            const uint32_t o = g * (uint32_t)sizeof(PT);
-            if constexpr (sizeof(PT) == 4) {
-                buf_store<uint32_t>(comp_rsrc(och_id), g * 4u, pid[k]);
-#pragma unroll
-                for (int q = 0; q < DIM; ++q) {
-                    buf_store<PT>(comp_rsrc(och + q * cs), o, px[k][q]);
-                    buf_store<PT>(comp_rsrc(och + (DIM + q) * cs), o, pv[k][q]);
-                }
-            } else {
-                *(uint32_t*)(och_id + g * 4u) = pid[k];
-#pragma unroll
-                for (int q = 0; q < DIM; ++q) {
-                    *(PT*)(och + q * cs + o) = px[k][q];
-                    *(PT*)(och + (DIM + q) * cs + o) = pv[k][q];
-                }
-            }
+            store_part<DIM, PT>(A.out, d.slot_off, g, px[k], pv[k], pid[k]);
         }
         // ---- sample windows to global memory
         if (A.do_fb && win_ok) {
@@ -1029,7 +974,7 @@ template <int DIM, typename PT, int NT, int PPT, int MODE, int OVF = 0>
 static hipError_t launch_p4(const ParticleLaunch& L, hipStream_t s) {
     PArgs<PT> a;
     a.D = L.D;
-    a.in.b = (unsigned char*)L.in.pos[0]; a.out.b = (unsigned char*)L.out.pos[0]; a.cs = L.cstride;
+    a.in = L.in; a.out = L.out;
     a.fill_in = L.fill_in; a.fill_out = L.fill_out; a.tile_inst = L.tile_inst;
     a.ufine = L.ufine; a.tfine = L.tfine; a.acc = L.acc; a.prof = L.prof; a.stats = L.stats; a.clock = L.clock;
     a.shifts = L.shifts;
@@ -1039,15 +984,18 @@ static hipError_t launch_p4(const ParticleLaunch& L, hipStream_t s) {
     a.xcd_per = L.xcd_blocked ? (L.tiles + 7) / 8 : 0;
     a.ovf = L.ovf;
     a.ovf_mode = OVF;
+    // the sample windows only where samples are taken: the other launches fit
+    // more workgroups per CU
+    const size_t lds = LDS_HDR + ((L.do_fb | L.do_prof) ? LDS_UNI : LDS_COLL);
     if constexpr (OVF == 2) {
         const long long grid = L.tiles < OVF_GRID ? L.tiles : OVF_GRID;
-        hipLaunchKernelGGL((k_particles_ovf<DIM, PT, NT, PPT, MODE>), dim3((unsigned)grid), dim3(NT), L.lds_bytes, s,
+        hipLaunchKernelGGL((k_particles_ovf<DIM, PT, NT, PPT, MODE>), dim3((unsigned)grid), dim3(NT), lds, s,
                            a);
         return hipGetLastError();
     } else {
         const long long grid = L.xcd_blocked ? 8 * a.xcd_per : L.tiles;
         auto kern = k_particles<DIM, PT, NT, PPT, MODE>;
-        hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NT), L.lds_bytes, s, a);
+        hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NT), lds, s, a);
         return hipGetLastError();
     }
 }
