@@ -85,7 +85,7 @@ struct lbmpcd_ctx {
     float* cl_stats = nullptr;     // [NSTATS] standardisation
     double* cl_sums = nullptr;     // [2 (NF + NOUT)] column sums
     double* cl_loss = nullptr;     // [1]
-    double* cl_facc = nullptr;     // [nslab][NF] feature sums of a collection window
+    double* cl_facc = nullptr;     // [11][band nodes] moment and shear-rate sums of a collection window
     double* cl_nm = nullptr;       // [nslab][10] particle moment sums
     float* cl_uc = nullptr;        // [nslab][3] LB velocity of each slab node (surrogate step)
     float* cl_M = nullptr;         // [band nodes][12] moments and shear rate (surrogate step)
@@ -452,7 +452,7 @@ int build(const lbmpcd_params* p, int n, std::vector<InstDesc>& D, Layout& L, lo
         L.cl_stats = take(4 * (size_t)NSTATS);
         L.cl_sums = take(8 * 2 * (size_t)(NF + NOUT));
         L.cl_loss = take(8);
-        L.cl_facc = take(8 * (size_t)slab * NF);
+        L.cl_facc = take(8 * (size_t)band * 11);
         L.cl_nm = take(8 * (size_t)slab * 10);
         L.cl_uc = take(4 * (size_t)slab * 3);
         L.cl_M = take(4 * (size_t)band * BMS);
@@ -790,8 +790,7 @@ int enqueue_one_step(lbmpcd_ctx* c, hipStream_t s) {
             return 0;
         }
         if (c->cl_collect)
-            HIPCHK(c, closure_features(c->lb_fp, c->d_desc, 0, c->cl_nslab, c->f[c->fcur], c->cl_facc, nullptr,
-                                       nullptr, nullptr, s));
+            HIPCHK(c, closure_features(c->lb_fp, c->d_desc, 0, c->total_band, c->f[c->fcur], c->cl_facc, s));
         if (c->mpcd) {
             HIPCHK(c, timed(c, 1, [&] {
                        return launch_band(c->dim, c->lb_fp, c->d_desc, c->n_inst, c->total_band, c->f[c->fcur],
@@ -1243,7 +1242,7 @@ int lbmpcd_closure_collect(lbmpcd_ctx* c, int32_t lb_steps, float* X, float* Y) 
     if (lb_steps < 1 || !X || !Y) return fail(c, LBMPCD_E_INVALID, "need lb_steps >= 1 and device X, Y");
     if (c->cl_on) return fail(c, LBMPCD_E_STATE, "collection runs the plain coupled step; disable the closure");
     const InstDesc& d = c->desc[0];
-    HIPCHK(c, hipMemsetAsync(c->cl_facc, 0, sizeof(double) * c->cl_nslab * NF, c->stream));
+    HIPCHK(c, hipMemsetAsync(c->cl_facc, 0, sizeof(double) * c->total_band * 11, c->stream));
     HIPCHK(c, hipMemsetAsync(c->cl_nm, 0, sizeof(double) * c->cl_nslab * 10, c->stream));
     for (int k = 0; k < lb_steps; ++k) {
         c->cl_collect = true;
@@ -1257,18 +1256,19 @@ int lbmpcd_closure_collect(lbmpcd_ctx* c, int32_t lb_steps, float* X, float* Y) 
         HIPCHK(c, closure_node_moments(c->part_fp, c->d_desc, 0, d.ntiles, c->part[c->pcur], c->fill[c->pcur],
                                        c->cl_nm, c->stream));
     }
-    HIPCHK(c, closure_collect_finish(c->cl_nslab, lb_steps, d.mass, c->cl_facc, c->cl_nm, X, Y, c->stream));
+    HIPCHK(c, closure_collect_finish(c->d_desc, 0, c->cl_nslab, c->total_band, lb_steps, d.mass, c->cl_facc,
+                                     c->cl_nm, X, Y, c->stream));
     return 0;
 }
 
 int lbmpcd_closure_features(lbmpcd_ctx* c, float* X) {
     if (int e = need_closure(c)) return e;
     if (!X) return fail(c, LBMPCD_E_INVALID, "X is null");
-    HIPCHK(c, hipMemsetAsync(c->cl_facc, 0, sizeof(double) * c->cl_nslab * NF, c->stream));
-    HIPCHK(c, closure_features(c->lb_fp, c->d_desc, 0, c->cl_nslab, c->f[c->fcur], c->cl_facc, nullptr, nullptr,
-                               nullptr, c->stream));
+    HIPCHK(c, hipMemsetAsync(c->cl_facc, 0, sizeof(double) * c->total_band * 11, c->stream));
+    HIPCHK(c, closure_features(c->lb_fp, c->d_desc, 0, c->total_band, c->f[c->fcur], c->cl_facc, c->stream));
     // one window of one step: the feature sums are the features
-    HIPCHK(c, closure_collect_finish(c->cl_nslab, 1, 1.0, c->cl_facc, nullptr, X, nullptr, c->stream));
+    HIPCHK(c, closure_collect_finish(c->d_desc, 0, c->cl_nslab, c->total_band, 1, 1.0, c->cl_facc, nullptr, X,
+                                     nullptr, c->stream));
     return 0;
 }
 

@@ -693,62 +693,49 @@ __device__ __forceinline__ void node_moments(const LT* fp, long long N, long lon
     for (int a = 0; a < 6; ++a) m[4 + a] = P[a];
 }
 
-// Features of one slab node: for the 27 neighbours (dz, dy, dx in -1..1, x
-// and z periodic, y clamped to the channel) the 10 moments, then the shear
-// rate sqrt(2 S:S) of the node with S = -(Pi - rho u u) / (2 rho c_s^2 tau).
+// The 10 moments and the shear rate sqrt(2 S:S), S = -(Pi - rho u u) /
+// (2 rho c_s^2 tau), of a node.
 template <typename LT>
-__global__ void __launch_bounds__(256) k_features(const InstDesc* __restrict__ D, int inst, long long nslab,
-                                                  const LT* __restrict__ f, double* facc, const float* st,
-                                                  uint16_t* Xb, float* uc) {
-    const long long sn = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (sn >= nslab) return;
-    const InstDesc& d = D[inst];
-    const int nsy = d.yhi - d.ylo;
-    const int x = (int)(sn % d.nx), y = d.ylo + (int)((sn / d.nx) % nsy), z = (int)(sn / ((long long)d.nx * nsy));
-    const LT* fp = f + d.node_off * Lat<3>::Q;
-    // each feature goes straight to its output as it is formed
-    auto emit = [&](int q, double v) {
-        if (facc) facc[sn * NF + q] += v;
-        if (Xb) Xb[sn * NFP + q] = to_bf16(((float)v - st[q]) * (1.0f / st[NF + q]));
-    };
-    int k = 0;
-    double mc[10];
-    for (int dz = -1; dz <= 1; ++dz)
-        for (int dy = -1; dy <= 1; ++dy)
-            for (int dx = -1; dx <= 1; ++dx) {
-                int xx = x + dx; if (xx < 0) xx += d.nx; else if (xx >= d.nx) xx -= d.nx;
-                int zz = z + dz; if (zz < 0) zz += d.nz; else if (zz >= d.nz) zz -= d.nz;
-                int yy = y + dy; yy = yy < 0 ? 0 : (yy >= d.ny ? d.ny - 1 : yy);
-                const long long n = ((long long)zz * d.ny + yy) * d.nx + xx;
-                double m[10];
-                node_moments<LT>(fp, d.N, n, d.g, m);
-                for (int q = 0; q < 10; ++q) emit(k + q, m[q]);
-                if (dx == 0 && dy == 0 && dz == 0)
-                    for (int q = 0; q < 10; ++q) mc[q] = m[q];
-                k += 10;
-            }
-    const double rho = mc[0], u[3] = {mc[1], mc[2], mc[3]};
-    if (uc)
-        for (int a = 0; a < 3; ++a) uc[sn * 3 + a] = (float)u[a];
+__device__ __forceinline__ void node_features(const LT* fp, const InstDesc& d, long long n, double m[11]) {
+    node_moments<LT>(fp, d.N, n, d.g, m);
+    const double rho = m[0], u[3] = {m[1], m[2], m[3]};
     const int A[6] = {0, 1, 2, 0, 0, 1}, B[6] = {0, 1, 2, 1, 2, 2};
     double ss = 0.0;
     for (int q = 0; q < 6; ++q) {
-        const double Sab = -(mc[4 + q] - rho * u[A[q]] * u[B[q]]) / (2.0 * rho * (1.0 / 3.0) * d.tau);
+        const double Sab = -(m[4 + q] - rho * u[A[q]] * u[B[q]]) / (2.0 * rho * (1.0 / 3.0) * d.tau);
         ss += (q < 3 ? 1.0 : 2.0) * Sab * Sab;
     }
-    emit(NF - 1, sqrt(2.0 * ss));
-    if (Xb)
-        for (int q = NF; q < NFP; ++q) Xb[sn * NFP + q] = 0;
+    m[10] = sqrt(2.0 * ss);
 }
 
-hipError_t closure_features(int lb_fp, const InstDesc* D, int inst, long long nslab, const void* f, double* facc,
-                            const float* stats, uint16_t* Xb, float* uc, hipStream_t s) {
+// Collection window: adds the moments and the shear rate of every band node
+// (the rows [by0, by0 + nyb) that the slab's 3x3x3 stencils reach) to its
+// FP64 sums facc[11][band nodes].  A slab node's 271 features are those of
+// its 27 neighbours, so the window's sums are kept per band node and spread
+// over the stencils once, at its end (k_collect_finish): summed per slab
+// node, with every neighbour's moments formed 27 times, a step of 16,384 slab
+// nodes took 216 us instead of 7.9, and the end of a window 132 us
+// instead of 20.7.
+template <typename LT>
+__global__ void __launch_bounds__(256) k_features(const InstDesc* __restrict__ D, int inst, long long nband,
+                                                  const LT* __restrict__ f, double* facc) {
+    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
+    if (i >= nband) return;
+    const InstDesc& d = D[inst];
+    const int x = (int)(i % d.nx), yb = (int)((i / d.nx) % d.nyb), z = (int)(i / ((long long)d.nx * d.nyb));
+    double m[11];
+    node_features<LT>(f + d.node_off * Lat<3>::Q, d, ((long long)z * d.ny + (d.by0 + yb)) * d.nx + x, m);
+#pragma unroll
+    for (int q = 0; q < 11; ++q) facc[q * nband + i] += m[q];
+}
+
+hipError_t closure_features(int lb_fp, const InstDesc* D, int inst, long long nband, const void* f, double* facc,
+                            hipStream_t s) {
     if (lb_fp == 64)
-        hipLaunchKernelGGL(k_features<double>, dim3(nblk(nslab)), dim3(256), 0, s, D, inst, nslab,
-                           (const double*)f, facc, stats, Xb, uc);
+        hipLaunchKernelGGL(k_features<double>, dim3(nblk(nband)), dim3(256), 0, s, D, inst, nband, (const double*)f,
+                           facc);
     else
-        hipLaunchKernelGGL(k_features<float>, dim3(nblk(nslab)), dim3(256), 0, s, D, inst, nslab,
-                           (const float*)f, facc, stats, Xb, uc);
+        hipLaunchKernelGGL(k_features<float>, dim3(nblk(nband)), dim3(256), 0, s, D, inst, nband, (const float*)f, facc);
     return hipGetLastError();
 }
 
@@ -824,19 +811,12 @@ __global__ void __launch_bounds__(256) k_band_moments(const InstDesc* __restrict
     if (i >= (long long)d.nx * nyb * d.nz) return;
     const int x = (int)(i % d.nx), yb = (int)((i / d.nx) % nyb), z = (int)(i / ((long long)d.nx * nyb));
     const long long n = ((long long)z * d.ny + (y0 + yb)) * d.nx + x;
-    double m[10];
-    node_moments<LT>(f + d.node_off * Lat<3>::Q, d.N, n, d.g, m);
-    const double rho = m[0], u[3] = {m[1], m[2], m[3]};
-    const int A[6] = {0, 1, 2, 0, 0, 1}, B[6] = {0, 1, 2, 1, 2, 2};
-    double ss = 0.0;
-    for (int q = 0; q < 6; ++q) {
-        const double Sab = -(m[4 + q] - rho * u[A[q]] * u[B[q]]) / (2.0 * rho * (1.0 / 3.0) * d.tau);
-        ss += (q < 3 ? 1.0 : 2.0) * Sab * Sab;
-    }
+    double m[11];
+    node_features<LT>(f + d.node_off * Lat<3>::Q, d, n, m);
     // binary32 is what the features use of them: (float)m - mean, then / std
     float* o = M + i * BMS;
     for (int q = 0; q < 10; ++q) o[q] = (float)m[q];
-    o[10] = (float)sqrt(2.0 * ss);
+    o[10] = (float)m[10];
     o[11] = 0.0f;
 }
 
@@ -1119,26 +1099,43 @@ hipError_t closure_node_moments(int part_fp, const InstDesc* D, int inst, long l
     return hipGetLastError();
 }
 
-__global__ void __launch_bounds__(256) k_collect_finish(long long nslab, int K, double mass, const double* facc,
-                                                        const double* nm, float* X, float* Y) {
-    const long long sn = (long long)blockIdx.x * 256 + threadIdx.x;
+// Averages of the window: one wave per slab node, lane: features lane, lane +
+// 64, ... (feature 10 e + q is moment q of stencil entry e = dz, dy, dx in
+// -1..1, x and z periodic, y clamped to the channel; the last is the node's
+// shear rate), then the targets.
+__global__ void __launch_bounds__(256) k_collect_finish(const InstDesc* __restrict__ D, int inst, long long nslab,
+                                                        long long nband, int K, double mass,
+                                                        const double* __restrict__ facc, const double* __restrict__ nm,
+                                                        float* X, float* Y) {
+    const long long sn = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (sn >= nslab) return;
-    for (int q = 0; q < NF; ++q) X[sn * NF + q] = (float)(facc[sn * NF + q] / K);
-    if (!Y) return;
+    const InstDesc& d = D[inst];
+    const int lane = threadIdx.x & 63, nsy = d.yhi - d.ylo;
+    const long long rw = sn / d.nx;
+    const int x = (int)(sn - rw * d.nx), y = d.ylo + (int)(rw % nsy), z = (int)(rw / nsy);
+    for (int k = lane; k < NF; k += 64) {
+        const int e = k < NF - 1 ? k / 10 : 13, q = k < NF - 1 ? k - 10 * e : 10;
+        int xx = x + e % 3 - 1; if (xx < 0) xx += d.nx; else if (xx >= d.nx) xx -= d.nx;
+        int zz = z + e / 9 - 1; if (zz < 0) zz += d.nz; else if (zz >= d.nz) zz -= d.nz;
+        int yy = y + (e / 3) % 3 - 1; yy = yy < 0 ? 0 : (yy >= d.ny ? d.ny - 1 : yy);
+        X[sn * NF + k] = (float)(facc[q * nband + ((long long)zz * d.nyb + (yy - d.by0)) * d.nx + xx] / K);
+    }
+    if (!Y || lane >= NOUT) return;
     const double* o = nm + sn * 10;
     const double cnt = o[0];
-    double u[3] = {0.0, 0.0, 0.0};
-    if (cnt > 0.0)
-        for (int a = 0; a < 3; ++a) u[a] = o[1 + a] / cnt;
-    for (int a = 0; a < 3; ++a) Y[sn * NOUT + a] = (float)u[a];
-    const int A[6] = {0, 1, 2, 0, 0, 1}, B[6] = {0, 1, 2, 1, 2, 2};
-    for (int q = 0; q < 6; ++q)
-        Y[sn * NOUT + 3 + q] = (float)(mass * (o[4 + q] - cnt * u[A[q]] * u[B[q]]) / K);
+    auto mean = [&](int a) { return cnt > 0.0 ? o[1 + a] / cnt : 0.0; };
+    if (lane < 3) {
+        Y[sn * NOUT + lane] = (float)mean(lane);
+    } else {
+        const int A[6] = {0, 1, 2, 0, 0, 1}, B[6] = {0, 1, 2, 1, 2, 2}, q = lane - 3;
+        Y[sn * NOUT + lane] = (float)(mass * (o[4 + q] - cnt * mean(A[q]) * mean(B[q])) / K);
+    }
 }
 
-hipError_t closure_collect_finish(long long nslab, int K, double mass, const double* facc, const double* nm,
-                                  float* X, float* Y, hipStream_t s) {
-    hipLaunchKernelGGL(k_collect_finish, dim3(nblk(nslab)), dim3(256), 0, s, nslab, K, mass, facc, nm, X, Y);
+hipError_t closure_collect_finish(const InstDesc* D, int inst, long long nslab, long long nband, int K, double mass,
+                                  const double* facc, const double* nm, float* X, float* Y, hipStream_t s) {
+    hipLaunchKernelGGL(k_collect_finish, dim3(nblk(nslab, 4)), dim3(256), 0, s, D, inst, nslab, nband, K, mass, facc, nm,
+                       X, Y);
     return hipGetLastError();
 }
 

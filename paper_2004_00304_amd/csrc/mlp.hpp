@@ -97,11 +97,10 @@ hipError_t mlp_refresh(const float* P32, uint16_t* Pf, hipStream_t s);
 // Column statistics of raw features / targets.
 hipError_t mlp_stats(const float* X, const float* Y, long long n, double* sums, float* stats, hipStream_t s);
 
-// Coupling: features of the slab nodes of one channel from its populations,
-// either raw into an FP64 accumulator (facc, [nslab][NF]) or standardised
-// into BF16 network inputs (Xb, [nslab][NFP]).
-hipError_t closure_features(int lb_fp, const InstDesc* D, int inst, long long nslab, const void* f,
-                            double* facc, const float* stats, uint16_t* Xb, float* uc, hipStream_t s);
+// Collection window: adds moments and shear rate of one channel's band nodes
+// to the FP64 sums facc, [11][nband].
+hipError_t closure_features(int lb_fp, const InstDesc* D, int inst, long long nband, const void* f, double* facc,
+                            hipStream_t s);
 // Network output -> feedback sums (count 1, predicted velocity) of every slab
 // node (unless acc is null); with do_prof also into the profile accumulators.
 // nsy: node rows of the slab.
@@ -121,9 +120,10 @@ hipError_t mlp_destandardize_uc(const float* Y, const float* stats, const float*
 // one workgroup per particle tile.
 hipError_t closure_node_moments(int part_fp, const InstDesc* D, int inst, long long ntiles, const PartBuf& buf,
                                 const uint32_t* fill, double* nm, hipStream_t s);
-// Averages of a collection window of K LB steps: features X [nslab][NF] and
-// targets Y [nslab][NOUT] (mean velocity, kinetic stress per unit volume).
-hipError_t closure_collect_finish(long long nslab, int K, double mass, const double* facc, const double* nm,
-                                  float* X, float* Y, hipStream_t s);
+// Averages of a collection window of K LB steps: features X [nslab][NF] from
+// the band nodes' sums and, unless Y is null, targets Y [nslab][NOUT] (mean
+// velocity, kinetic stress per unit volume).
+hipError_t closure_collect_finish(const InstDesc* D, int inst, long long nslab, long long nband, int K, double mass,
+                                  const double* facc, const double* nm, float* X, float* Y, hipStream_t s);
 
 }  // namespace lbmpcd
