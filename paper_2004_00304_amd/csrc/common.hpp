@@ -52,6 +52,7 @@ struct InstDesc {
     // particle tiles
     int Tx, Ty, Tz, ntx, nty, ntz, cap, nct;
     int lTx, lTy, lTz, lr; // log2 of the tile sides (powers of two) and of r (-1 if r is not one)
+    int lrep, pad4;       // log2 of the replicas of a cell's sums in the collision (512 threads)
     long long ntiles, tile_off, slot_off;
     // band (rows of node velocities used by the interpolation)
     int by0, nyb;

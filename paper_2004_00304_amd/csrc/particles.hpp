@@ -29,6 +29,7 @@
 #pragma once
 
 #include <cmath>
+#include <type_traits>
 
 #include "common.hpp"
 #include "launch.hpp"
@@ -258,6 +259,13 @@ __device__ __forceinline__ void particle_tile(const PArgs<PT>& A, long long T, u
     unsigned char* uni = smem + LDS_HDR;
     double* wacc = (double*)uni;                // [MAX_WIN][NREP][4] node sample window
     double* wprof = wacc + MAX_WIN * NREP * 4;  // [4][rows][slots] profile window
+    // Cell sums: in tiles of at most four cells (hundreds of particles per
+    // cell, which 512 threads serve) every cell keeps 32 replicas, lane l
+    // adding into replica l mod 32, so that a cell's particles do not all meet
+    // on one address.  Coupled step of the paper's channels at 1,000 particles
+    // per cell, MPCD-AT: centre line 39.8 -> 35.4 us, near the wall 56.9 ->
+    // 50.9.  More cells per tile measure slower with replicas (2D channel with
+    // eight per cell 51.1 -> 52.9 us).
     uint32_t* ccnt = (uint32_t*)uni;                 // [MAX_NCT]
     double* csv = (double*)(uni + MAX_NCT * 4);      // [MAX_NCT][3]
     double* cvcm = csv + MAX_NCT * 3;                // [MAX_NCT][3]
@@ -294,6 +302,8 @@ __device__ __forceinline__ void particle_tile(const PArgs<PT>& A, long long T, u
         return;
     }
     if (n > (uint32_t)cap) n = (uint32_t)cap;
+    constexpr bool REPS = NT == 512;  // elsewhere the replicas' code alone costs MPCD-AT 5 %
+    [[maybe_unused]] const int lrep = REPS ? d.lrep : 0;
     const long long t_now = *cptr(A.clock);
     const PT rr = (PT)d.r;
     cst<double>* shtab = cptr(A.shifts) + (long long)ii * 2 * d.S * 3;
@@ -363,7 +373,7 @@ __device__ __forceinline__ void particle_tile(const PArgs<PT>& A, long long T, u
             const uint32_t cg = (uint32_t)(ix + d.Cx * (iy + d.CyB * iz));
             const U4 w = AT ? U4{0u, 0u, 0u, 0u} : rng_block(kfresh(), cg, tc, sc, P_ROT, 0);
             if constexpr (AT) {
-                crot[3 * j] = 0.0; crot[3 * j + 1] = 0.0; crot[3 * j + 2] = 0.0;
+                if constexpr (!REPS) { crot[3 * j] = 0.0; crot[3 * j + 1] = 0.0; crot[3 * j + 2] = 0.0; }
             } else if constexpr (DIM == 2) {
                 crot[3 * j] = (w.x & 1u) ? 1.0 : -1.0;
             } else {
@@ -376,8 +386,17 @@ __device__ __forceinline__ void particle_tile(const PArgs<PT>& A, long long T, u
                 crot[3 * j + 1] = sxy * sp;
                 crot[3 * j + 2] = nz;
             }
-            ccnt[j] = 0u;
-            csv[3 * j] = 0.0; csv[3 * j + 1] = 0.0; csv[3 * j + 2] = 0.0;
+            if constexpr (!REPS) {
+                ccnt[j] = 0u;
+                csv[3 * j] = 0.0; csv[3 * j + 1] = 0.0; csv[3 * j + 2] = 0.0;
+            }
+        }
+        if constexpr (REPS) {
+            for (int j = tid; j < (d.nct << lrep); j += NT) {
+                ccnt[j] = 0u;
+                csv[3 * j] = 0.0; csv[3 * j + 1] = 0.0; csv[3 * j + 2] = 0.0;
+                if constexpr (AT) { crot[3 * j] = 0.0; crot[3 * j + 1] = 0.0; crot[3 * j + 2] = 0.0; }
+            }
         }
     }
 #pragma unroll
@@ -414,9 +433,10 @@ __device__ __forceinline__ void particle_tile(const PArgs<PT>& A, long long T, u
             }
             const int c = lx + ((ly + (lz << d.lTy)) << d.lTx);
             lc[k] = c;
-            atomicAdd(&ccnt[c], 1u);
+            const int cr = REPS ? (c << lrep) | (lane & ((1 << lrep) - 1)) : c;
+            atomicAdd(&ccnt[cr], 1u);
 #pragma unroll
-            for (int q = 0; q < DIM; ++q) sum_lds<DET>(&csv[3 * c + q], (double)pv[k][q]);
+            for (int q = 0; q < DIM; ++q) sum_lds<DET>(&csv[3 * cr + q], (double)pv[k][q]);
             if constexpr (AT) {
                 double z[3];
                 if constexpr (sizeof(PT) == 4) {
@@ -430,7 +450,7 @@ __device__ __forceinline__ void particle_tile(const PArgs<PT>& A, long long T, u
 #pragma unroll
                 for (int q = 0; q < DIM; ++q) {
                     vr[k][q] = (PT)(d.sd * z[q]);
-                    sum_lds<DET>(&crot[3 * c + q], (double)vr[k][q]);
+                    sum_lds<DET>(&crot[3 * cr + q], (double)vr[k][q]);
                 }
             }
         }
@@ -438,7 +458,27 @@ __device__ __forceinline__ void particle_tile(const PArgs<PT>& A, long long T, u
         for (int j = tid; j < d.nct; j += NT) {
             const int lx = j & (d.Tx - 1), ly = (j >> d.lTx) & (d.Ty - 1), lz = j >> (d.lTx + d.lTy);
             const int ix = (tx << d.lTx) + lx, iy = (ty << d.lTy) + ly, iz = (tz << d.lTz) + lz;
-            const uint32_t nc = ccnt[j];
+            const int jr = REPS ? j << lrep : j;
+            uint32_t nc = ccnt[jr];
+            if constexpr (REPS) {
+                // the replicas' sums into the first
+                using Sum = std::conditional_t<DET, unsigned long long, double>;
+                Sum *sv = (Sum*)csv, *sr = (Sum*)crot, v[3] = {0, 0, 0}, r[3] = {0, 0, 0};
+                nc = 0u;
+                for (int i = jr; i < (j + 1) << lrep; ++i) {
+                    nc += ccnt[i];
+#pragma unroll
+                    for (int q = 0; q < DIM; ++q) {
+                        v[q] += sv[3 * i + q];
+                        if constexpr (AT) r[q] += sr[3 * i + q];
+                    }
+                }
+#pragma unroll
+                for (int q = 0; q < DIM; ++q) {
+                    sv[3 * jr + q] = v[q];
+                    if constexpr (AT) sr[3 * jr + q] = r[q];
+                }
+            }
             if (nc == 0u || ix >= d.Cx || iy >= d.CyB || iz >= d.Cz) continue;
             const uint32_t cg = (uint32_t)(ix + d.Cx * (iy + d.CyB * iz));
             // wall-cut cell below its nominal occupancy: nv virtual particles
@@ -458,11 +498,11 @@ __device__ __forceinline__ void particle_tile(const PArgs<PT>& A, long long T, u
 #pragma unroll
             for (int q = 0; q < 3; ++q) cvcm[3 * j + q] = 0.0;
 #pragma unroll
-            for (int q = 0; q < DIM; ++q) cvcm[3 * j + q] = (sum_read<DET>(&csv[3 * j + q]) + pvv[q]) / ((double)nc + mv);
+            for (int q = 0; q < DIM; ++q) cvcm[3 * j + q] = (sum_read<DET>(&csv[3 * jr + q]) + pvv[q]) / ((double)nc + mv);
             if constexpr (AT) {
                 // mean random velocity over the cell's real particles
 #pragma unroll
-                for (int q = 0; q < DIM; ++q) crot[3 * j + q] = sum_read<DET>(&crot[3 * j + q]) / (double)nc;
+                for (int q = 0; q < DIM; ++q) crot[3 * jr + q] = sum_read<DET>(&crot[3 * jr + q]) / (double)nc;
             }
             if (A.cell_vcm && ii == A.diag_inst) {
 #pragma unroll
@@ -479,7 +519,7 @@ __device__ __forceinline__ void particle_tile(const PArgs<PT>& A, long long T, u
             if constexpr (AT) {
                 // Eq. 6: centre of mass plus the random velocity less the cell mean
 #pragma unroll
-                for (int q = 0; q < DIM; ++q) pv[k][q] = (PT)(vc[q] + ((double)vr[k][q] - crot[3 * c + q]));
+                for (int q = 0; q < DIM; ++q) pv[k][q] = (PT)(vc[q] + ((double)vr[k][q] - crot[3 * (REPS ? c << lrep : c) + q]));
                 continue;
             }
             double wv[3] = {0.0, 0.0, 0.0}, rv[3];
