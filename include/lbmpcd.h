@@ -149,7 +149,9 @@ typedef struct lbmpcd_params {
     uint32_t instance;     /* instance number inside the key */
     int32_t tile[3];       /* particle tile in cells per axis (powers of two); 0 = from tile_target */
     double capacity_factor;/* tile capacity / expected occupancy; 0 = default 1.3 */
-    int32_t tile_target;   /* expected particles per tile when tile[] is 0; 0 = default 1280 */
+    int32_t tile_target;   /* expected particles per tile when tile[] is 0; 0 = default: 1280,
+                              and less where the context's channels would make fewer than
+                              2560 such tiles (640; in 2D below 512 320, below 128 160) */
     int32_t wg_threads;    /* particle kernel workgroup: 128, 256 or 512 threads; 0 = 256,
                               or 512 for binary64 particles in tiles of over 1024 slots
                               unless the six-slot form applies.  Six-slot form: at 256
@@ -330,8 +332,8 @@ typedef struct lbmpcd_tuning {
     int32_t wg_threads;    /* chosen workgroup size */
     int32_t tried;         /* candidates measured */
     double ms_per_step;    /* ms per coupled LB step of the chosen candidate */
-    double ms_default;     /* ms per coupled LB step of the library's default shape (tile
-                              target 1280, its default workgroup, schedule 0), -1 if not
+    double ms_default;     /* ms per coupled LB step of the library's default shape (its
+                              default tile target and workgroup, schedule 0), -1 if not
                               measured */
     int32_t schedule;      /* chosen tile order */
 } lbmpcd_tuning;

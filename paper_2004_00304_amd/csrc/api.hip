@@ -133,11 +133,27 @@ int ilog2(int v) {
     return l;
 }
 
-int choose_tile(const lbmpcd_params& p, Geometry& g, std::string& msg) {
+// Default tile size in expected particles.  Tiles of 1280 amortise a tile's
+// barriers and tables best, but up to 1280 workgroups are resident at once
+// (five per CU), and a grid of fewer tiles leaves CUs idle while each tile
+// takes its full latency: smaller grids take smaller tiles.  Coupled step, us,
+// tiles of 1280 / the rule's: 2D channel (66 tiles of 1280) 69.1 / 51.2 at 160,
+// four times as long (264) 86.6 / 76.7 at 320; 3D slab of 1.8M binary32
+// particles (1,512) 237 / 216 at 640; 3D channel cut by 64 (2,200) 265 / 259.
+// The next larger ones gain nothing: eight channels of the ensemble (3,150)
+// 409 / 419, 3D channel cut by 16 (8,700) 717 / 825.  In 3D, where a smaller
+// tile has more surface, 640 serves all grids below (168 tiles: 111.7 / 84.3,
+// 75.4 at 320; 693 tiles: 153 / 128, 144 at 320).
+constexpr int TILE_TARGET = 1280;
+int tile_target_for(int dim, long long tiles_of_1280) {
+    if (tiles_of_1280 >= 2560) return TILE_TARGET;
+    return dim == 3 || tiles_of_1280 >= 512 ? 640 : tiles_of_1280 >= 128 ? 320 : 160;
+}
+
+int choose_tile(const lbmpcd_params& p, int target_default, Geometry& g, std::string& msg) {
     int T[3] = {p.tile[0], p.tile[1], p.tile[2]};
     if (T[0] <= 0 || T[1] <= 0 || (p.dim == 3 && T[2] <= 0)) {
-        // aim at ~1280 expected particles per tile
-        const int per_tile = p.tile_target > 0 ? p.tile_target : 1280;
+        const int per_tile = p.tile_target > 0 ? p.tile_target : target_default;
         int target = std::max(8, std::min(MAX_NCT, per_tile / std::max(1, p.ppc)));
         // shapes below 8 cells serve only dense cells (hundreds of particles
         // per cell, as in the paper's runs), whose tiles would overflow
@@ -213,7 +229,7 @@ int choose_tile(const lbmpcd_params& p, Geometry& g, std::string& msg) {
     return 0;
 }
 
-int geometry(const lbmpcd_params& p, Geometry& g, std::string& msg) {
+int geometry(const lbmpcd_params& p, Geometry& g, std::string& msg, int target_default = TILE_TARGET) {
     if (!p.mpcd) return 0;
     const int r = p.refine;
     g.R = (p.yhi - p.ylo) * r;
@@ -225,7 +241,7 @@ int geometry(const lbmpcd_params& p, Geometry& g, std::string& msg) {
     g.top_wall = (p.walls_y && p.yhi == p.n[1]) ? 1 : 0;
     g.ncells = (long long)g.Cx * g.CyB * g.Cz;
     g.Np = (long long)g.Cx * g.R * g.Cz * p.ppc;
-    if (choose_tile(p, g, msg)) return 1;
+    if (choose_tile(p, target_default, g, msg)) return 1;
     g.ntx = (g.Cx + g.Tx - 1) / g.Tx;
     g.nty = (g.CyB + g.Ty - 1) / g.Ty;
     g.ntz = (g.Cz + g.Tz - 1) / g.Tz;
@@ -353,15 +369,28 @@ struct Layout {
     size_t acc_bytes, prof_bytes, scratch_bytes;
 };
 
+// Default tile target of a context's channels: a channel whose tile shape or
+// size is given counts with that.
+int context_target(const lbmpcd_params* p, int n) {
+    long long tiles = 0;
+    std::string msg;
+    for (int i = 0; i < n; ++i) {
+        Geometry g;
+        if (geometry(p[i], g, msg)) return TILE_TARGET;
+        tiles += g.ntiles;
+    }
+    return tile_target_for(p[0].dim, tiles);
+}
+
 int build(const lbmpcd_params* p, int n, std::vector<InstDesc>& D, Layout& L, long long tot[7], std::string& msg) {
     D.assign(n, InstDesc{});
     long long node = 0, band = 0, ufine = 0, tiles = 0, slots = 0, parts = 0, slab = 0, prow = 0;
     size_t max_field = 0;
-    const int Q = p[0].dim == 2 ? 9 : 19;
+    const int Q = p[0].dim == 2 ? 9 : 19, target = context_target(p, n);
     for (int i = 0; i < n; ++i) {
         const lbmpcd_params& q = p[i];
         Geometry g;
-        if (geometry(q, g, msg)) return LBMPCD_E_INVALID;
+        if (geometry(q, g, msg, target)) return LBMPCD_E_INVALID;
         InstDesc& d = D[i];
         d.nx = q.n[0]; d.ny = q.n[1]; d.nz = q.n[2]; d.walls_y = q.walls_y;
         d.N = (long long)q.n[0] * q.n[1] * q.n[2];
@@ -1157,6 +1186,9 @@ int lbmpcd_autotune(const lbmpcd_params* p, int32_t n_inst, void* dev_workspace,
         return fail(nullptr, LBMPCD_E_DEVICE, "event creation failed");
     }
     static const int targets[] = {160, 320, 640, 1280};
+    std::vector<lbmpcd_params> q0(p, p + n_inst);
+    for (auto& x : q0) x.tile_target = 0;
+    const int tt_default = context_target(q0.data(), n_inst);
     static const int wgs[] = {256, 512};
     std::vector<lbmpcd_params> q(p, p + n_inst);
     double best = -1.0;
@@ -1193,7 +1225,7 @@ int lbmpcd_autotune(const lbmpcd_params* p, int32_t n_inst, void* dev_workspace,
             lbmpcd_destroy(c);
             const double per = (double)ms / lb_steps;
             ++out->tried;
-            if (tt == 1280 && wg == default_wg && sched == 0) out->ms_default = per;
+            if (tt == tt_default && wg == default_wg && sched == 0) out->ms_default = per;
             if (best < 0 || per < best) {
                 best = per;
                 out->tile_target = tt;
