@@ -18,7 +18,7 @@ __device__ __forceinline__ double poiseuille_p(const InstDesc& d, double gk, dou
 
 template <int DIM, typename PT>
 __global__ void __launch_bounds__(WG) k_part_init(const InstDesc* __restrict__ D, int n_inst, long long total,
-                                                  PStore<DIM, PT> P) {
+                                                  PartBuf P) {
     long long gid = (long long)blockIdx.x * WG + threadIdx.x;
     if (gid >= total) return;
     int ii = find_inst(D, n_inst, gid, [](const InstDesc& d) { return d.part_off; });
@@ -42,16 +42,14 @@ __global__ void __launch_bounds__(WG) k_part_init(const InstDesc* __restrict__ D
     const long long tile = tx + (long long)d.ntx * (ty + (long long)d.nty * tz);
     const long long lcell = (I - tx * d.Tx) + (long long)cx * ((J - ty * d.Ty) + (long long)cy * (K - tz * d.Tz));
     const long long slot = lcell * d.ppc + id % d.ppc;
-    const long long g = d.slot_off + tile * d.cap + slot;
-    *P.id(g) = (uint32_t)id;
-    *P.pos(0, g) = (PT)x;
-    *P.pos(1, g) = (PT)y;
-    if (DIM == 3) *P.pos(2, g) = (PT)zz;
+    const PT px[3] = {(PT)x, (PT)y, (PT)zz};
+    PT pv[3];
 #pragma unroll
     for (int q = 0; q < DIM; ++q) {
         const double u0 = d.init_flow ? poiseuille_p(d, d.g[q], y) : 0.0;
-        *P.vel(q, g) = (PT)(u0 + d.sd * z[q]);
+        pv[q] = (PT)(u0 + d.sd * z[q]);
     }
+    store_part<DIM, PT>(P, d.slot_off, (uint32_t)(tile * d.cap + slot), px, pv, (uint32_t)id);
 }
 
 __global__ void __launch_bounds__(WG) k_fill_sequential(const InstDesc* __restrict__ D, int n_inst, long long tiles,
@@ -231,10 +229,10 @@ hipError_t launch_part_init(int dim, int part_fp, const InstDesc* D, int n_inst,
                             hipStream_t s) {
     if (total <= 0) return hipSuccess;
     dim3 g(nblk(total)), b(WG);
-    if (dim == 2 && part_fp == 64) hipLaunchKernelGGL((k_part_init<2, double>), g, b, 0, s, D, n_inst, total, typed<2, double>(buf));
-    else if (dim == 2) hipLaunchKernelGGL((k_part_init<2, float>), g, b, 0, s, D, n_inst, total, typed<2, float>(buf));
-    else if (part_fp == 64) hipLaunchKernelGGL((k_part_init<3, double>), g, b, 0, s, D, n_inst, total, typed<3, double>(buf));
-    else hipLaunchKernelGGL((k_part_init<3, float>), g, b, 0, s, D, n_inst, total, typed<3, float>(buf));
+    if (dim == 2 && part_fp == 64) hipLaunchKernelGGL((k_part_init<2, double>), g, b, 0, s, D, n_inst, total, buf);
+    else if (dim == 2) hipLaunchKernelGGL((k_part_init<2, float>), g, b, 0, s, D, n_inst, total, buf);
+    else if (part_fp == 64) hipLaunchKernelGGL((k_part_init<3, double>), g, b, 0, s, D, n_inst, total, buf);
+    else hipLaunchKernelGGL((k_part_init<3, float>), g, b, 0, s, D, n_inst, total, buf);
     return hipGetLastError();
 }
 
