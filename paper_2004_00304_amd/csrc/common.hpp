@@ -182,13 +182,13 @@ __device__ __forceinline__ void rng_normals32(Key k, uint32_t elem, uint32_t t, 
                                               uint32_t purpose, float z[3]) {
     const U4 w = rng_block(k, elem, t, sub, purpose, 0);
     float s, c;
-    const float r0 = sqrtf(-2.0f * ln_unit32(1.0f - (float)(w.x >> 8) * 0x1p-24f));
+    const float r0 = root32(-2.0f * ln_unit32(1.0f - (float)(w.x >> 8) * 0x1p-24f));
     sincos_2pi32((float)(w.y >> 8) * 0x1p-24f, &s, &c);
     z[0] = r0 * c;
     z[1] = r0 * s;
     z[2] = 0.0f;
     if constexpr (DIM == 3) {
-        const float r1 = sqrtf(-2.0f * ln_unit32(1.0f - (float)(w.z >> 8) * 0x1p-24f));
+        const float r1 = root32(-2.0f * ln_unit32(1.0f - (float)(w.z >> 8) * 0x1p-24f));
         sincos_2pi32((float)(w.w >> 8) * 0x1p-24f, &s, &c);
         z[2] = r1 * c;
     }
@@ -246,6 +246,14 @@ struct DevStats {
 
 __device__ __forceinline__ int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
 
+// (int)floor(t); binary32 in one instruction.
+__device__ __forceinline__ int floor_int(double t) { return (int)floor(t); }
+__device__ __forceinline__ int floor_int(float t) {
+    int i;
+    asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(i) : "v"(t));
+    return i;
+}
+
 // One coordinate of the shifted-grid cell, floor((x - lo + shift) * r),
 // evaluated in the particle store precision.
 template <typename PT>
@@ -253,7 +261,7 @@ __device__ __forceinline__ int bin_coord(PT x, PT lo, PT sh, PT r) {
     PT t = x - lo;
     t = t + sh;
     t = t * r;
-    return (int)floor(t);
+    return floor_int(t);
 }
 
 // Row of the shifted grid of a slab position, periodic across the slab when

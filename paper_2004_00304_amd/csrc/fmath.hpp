@@ -92,6 +92,34 @@ LBMPCD_HD void sincos_2pi(double u, double* sn, double* cs) {
     *cs = (qm == 1 || qm == 2) ? -b : b;
 }
 
+// Quotient and square root of the binary32 pair's domains, correctly rounded
+// like the IEEE operations but without their scaling and special cases (on the
+// device about 11 and 16 instructions each): Newton steps with exact residuals
+// on the hardware's reciprocal and reciprocal root.  quot32: a in [-0.3, 0.42],
+// b in [1.7, 2.5]; root32: x = 0 or x in [2^-25, 64].  Equal to the IEEE
+// results for every argument the transform can produce.
+LBMPCD_HD float quot32(float a, float b) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    float r = __builtin_amdgcn_rcpf(b);
+    r = fmaf(fmaf(-b, r, 1.0f), r, r);
+    const float q = a * r;
+    return fmaf(fmaf(-b, q, a), r, q);
+#else
+    return a / b;
+#endif
+}
+
+LBMPCD_HD float root32(float x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    const float h = __builtin_amdgcn_rsqf(x);
+    const float g = x * h;
+    const float r = fmaf(fmaf(-g, g, x), 0.5f * h, g);
+    return x > 0.0f ? r : x;
+#else
+    return sqrtf(x);
+#endif
+}
+
 LBMPCD_HD float ln_unit32(float x) {
     int e;
     float m = frexpf(x, &e);  // x = m 2^e, m in [1/2, 1)
@@ -100,7 +128,7 @@ LBMPCD_HD float ln_unit32(float x) {
         e -= 1;
     }
     const float f = m - 1.0f;  // exact
-    const float s = f / (2.0f + f);
+    const float s = quot32(f, 2.0f + f);
     const float z = s * s;
     float p = 1.0f / 9.0f;
     p = fmaf(p, z, 1.0f / 7.0f);
