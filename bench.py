@@ -37,7 +37,8 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0  # MI355X HBM3E, 8 TB/s
 # every source the coupled step's kernels are compiled from, and the flags
-KERNEL_SOURCES = ["paper_2004_00304_amd/csrc/particles.hpp", "paper_2004_00304_amd/csrc/kernels_mpcd.hip",
+KERNEL_SOURCES = ["paper_2004_00304_amd/csrc/particles.hpp", "paper_2004_00304_amd/csrc/pstore.hpp",
+                  "paper_2004_00304_amd/csrc/kernels_mpcd.hip",
                   "paper_2004_00304_amd/csrc/kernels_mpcd_ce.hip", "paper_2004_00304_amd/csrc/common.hpp",
                   "paper_2004_00304_amd/csrc/fmath.hpp", "paper_2004_00304_amd/csrc/launch.hpp",
                   "paper_2004_00304_amd/csrc/kernels_lb.hip", "paper_2004_00304_amd/build.py"]
