@@ -31,11 +31,13 @@
 // of the cycles), so what every particle executes is kept short: one test for
 // both periodic axes, wrapped only where it fails; the body of the boundary
 // conditions alone checks for finite velocities; the exchange is decided by
-// comparing positions; fused multiply-adds in the rotation; 24-bit products
-// in the tile index, and none in the slot of a store; the normals' quotients
-// and roots without the IEEE sequences' range handling (thin film 5.38 -> 5.14
-// ms per MPCD step, 3D channel 2.39 -> 2.31, with MPCD-AT 3.08 -> 2.97; the
-// binary64 ensemble, bound by latency, 2.10 -> 2.09).
+// comparing positions; 24-bit products in the tile index, and none in the slot
+// of a store; the normals' quotients and roots without the IEEE sequences'
+// range handling (thin film 5.38 -> 5.19 ms per MPCD step, 3D channel 2.39 ->
+// 2.32, with MPCD-AT 3.08 -> 2.96; the binary64 ensemble, bound by latency,
+// 2.10 -> 2.09).  All of it gives the same bits; fused multiply-adds in the
+// rotation would not (film 5.12, 3D channel 2.30): a rounding that differs
+// makes another realisation of every long run.
 #pragma once
 
 #include <cmath>
@@ -538,17 +540,17 @@ __device__ __forceinline__ void particle_tile(const PArgs<PT>& A, long long T, u
             for (int q = 0; q < DIM; ++q) wv[q] = (double)pv[k][q] - vc[q];
             if constexpr (DIM == 2) {
                 const double s = crot[3 * c] * sa;
-                rv[0] = fma(-s, wv[1], ca * wv[0]);
-                rv[1] = fma(s, wv[0], ca * wv[1]);
+                rv[0] = ca * wv[0] - s * wv[1];
+                rv[1] = s * wv[0] + ca * wv[1];
             } else {
                 const double a0 = crot[3 * c], a1 = crot[3 * c + 1], a2 = crot[3 * c + 2];
-                const double nw = one_c * fma(a2, wv[2], fma(a1, wv[1], a0 * wv[0]));
-                const double cx = fma(a1, wv[2], -(a2 * wv[1]));
-                const double cy = fma(a2, wv[0], -(a0 * wv[2]));
-                const double cz = fma(a0, wv[1], -(a1 * wv[0]));
-                rv[0] = fma(a0, nw, fma(cx, sa, wv[0] * ca));
-                rv[1] = fma(a1, nw, fma(cy, sa, wv[1] * ca));
-                rv[2] = fma(a2, nw, fma(cz, sa, wv[2] * ca));
+                const double nw = a0 * wv[0] + a1 * wv[1] + a2 * wv[2];
+                const double cx = a1 * wv[2] - a2 * wv[1];
+                const double cy = a2 * wv[0] - a0 * wv[2];
+                const double cz = a0 * wv[1] - a1 * wv[0];
+                rv[0] = wv[0] * ca + cx * sa + a0 * nw * one_c;
+                rv[1] = wv[1] * ca + cy * sa + a1 * nw * one_c;
+                rv[2] = wv[2] * ca + cz * sa + a2 * nw * one_c;
             }
 #pragma unroll
             for (int q = 0; q < DIM; ++q) pv[k][q] = (PT)(vc[q] + rv[q]);
