@@ -15,6 +15,7 @@
 #include "../../include/lbmpcd.h"
 #include "common.hpp"
 #include "mlp.hpp"
+#include "slab.hpp"
 #include "launch.hpp"
 
 using namespace lbmpcd;
@@ -416,6 +417,7 @@ int build(const lbmpcd_params* p, int n, std::vector<InstDesc>& D, Layout& L, lo
         for (int k = 0; k < 3; ++k) { d.gh[k] = 0.5 * q.g[k] * d.dt; d.gdt[k] = q.g[k] * d.dt; }
         for (int k = 0; k < 3; ++k) { d.ghf[k] = (float)d.gh[k]; d.gdtf[k] = (float)d.gdt[k]; }
         d.dtf = (float)d.dt;
+        buffer_bounds(q.ylo, q.yhi, q.buf_lo, q.buf_hi, &d.buf_below, &d.buf_from);
         d.sd = q.mass > 0 ? std::sqrt(q.kT / q.mass) : 0.0;
         const double alpha = q.alpha_deg * 3.141592653589793 / 180.0;
         d.cos_a = std::cos(alpha);

@@ -64,6 +64,7 @@ struct InstDesc {
     // MPCD constants
     double a, dt, gh[3], gdt[3], sd, cos_a, sin_a, mass, kT;
     float ghf[3], gdtf[3], dtf, padf;  // binary32 roundings of gh, gdt, dt (binary32 particles)
+    float buf_below, buf_from;         // bounds of the buffers in y (buffer_bounds, binary32 particles)
     uint32_t key0, key1;
     int S, pad2;          // MPCD steps per LB step
     // Chapman-Enskog exchange: T = ce_scale dev(-Pi_neq) / rho at the band nodes

@@ -601,7 +601,7 @@ __device__ __forceinline__ void particle_tile(const PArgs<PT>& A, long long T, u
         const PT ylo_p = (PT)d.ylo, yhi_p = (PT)d.yhi;
         const int bw = d.bot_wall, tw = d.top_wall, ywrap = d.ywrap;
         const int rb_lo = d.buf_lo * d.r, rb_hi = d.R - d.buf_hi * d.r;
-        [[maybe_unused]] const PT yblo_p = (PT)(d.ylo + d.buf_lo), ybhi_p = (PT)(d.yhi - d.buf_hi);
+        [[maybe_unused]] const float buf_below = d.buf_below, buf_from = d.buf_from;
         auto row_of = [&](PT y) { return clampi((int)floor(((double)y - ylo_d) * (double)d.r), 0, d.R - 1); };
         const long long NF = (long long)d.Cx * d.NB * d.Cz;
         const double* uf = A.ufine + d.ufine_off * DIM;
@@ -630,9 +630,8 @@ __device__ __forceinline__ void particle_tile(const PArgs<PT>& A, long long T, u
             int J0 = 0;
             bool in_buf;
             if constexpr (sizeof(PT) == 4) {
-                // y - ylo and its product with r are exact in binary64, so the
-                // row lies in a buffer exactly where y does
-                in_buf = px[k][1] < yblo_p || px[k][1] >= ybhi_p;
+                // the row's rule by comparisons alone (buffer_bounds)
+                in_buf = px[k][1] < buf_below || px[k][1] >= buf_from;
             } else {
                 J0 = row_of(px[k][1]);
                 in_buf = J0 < rb_lo || J0 >= rb_hi;
