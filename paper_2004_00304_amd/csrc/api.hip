@@ -985,14 +985,14 @@ int produce(lbmpcd_ctx* c, int32_t field, int32_t inst, void* dst, size_t nbytes
             if (field == LBMPCD_PART_VEL)
                 if (int e = finalize(c)) return e;
             HIPCHK(c, launch_gather(c->dim, c->part_fp, c->d_desc, inst, d, c->part[c->pcur],
-                                    c->fill[c->pcur], field == LBMPCD_PART_POS ? (double*)dst : nullptr,
+                                    c->fill[c->pcur], c->stats, field == LBMPCD_PART_POS ? (double*)dst : nullptr,
                                     field != LBMPCD_PART_POS ? (double*)dst : nullptr, nullptr,
                                     c->part[c->pcur ^ 1].b, tl, sl, s));
             return 0;
         case LBMPCD_CELL_ID:
             if (c->t == 0) return fail(c, LBMPCD_E_STATE, "no binning before the first step");
             HIPCHK(c, launch_gather(c->dim, c->part_fp, c->d_desc, inst, d, c->part[c->pcur],
-                                    c->fill[c->pcur], nullptr, nullptr, (int*)dst, nullptr, tl, sl, s));
+                                    c->fill[c->pcur], c->stats, nullptr, nullptr, (int*)dst, nullptr, tl, sl, s));
             return 0;
         case LBMPCD_CELL_COUNT:
             if (c->t == 0) return fail(c, LBMPCD_E_STATE, "no binning before the first step");

@@ -120,18 +120,27 @@ __global__ void __launch_bounds__(WG) k_scatter(const InstDesc* __restrict__ D, 
 }
 
 // Positions or velocities in id order through the slots of the ids: one thread
-// per id, the stores consecutive.
+// per id, the stores consecutive.  An id that a tile overflow lost has no slot,
+// and its word of the map is whatever the memory held: once particles have been
+// dropped, an entry counts only if it names a filled slot with that id in it
+// (the others then cost their id's load; marking the map beforehand would cost
+// every read a pass over it and a launch).
 template <int DIM, typename PT, int WHAT>
 __global__ void __launch_bounds__(WG) k_gather(const InstDesc* __restrict__ D, int inst, PartBuf P,
+                                               const uint32_t* __restrict__ fill, const DevStats* __restrict__ stats,
                                                const uint32_t* __restrict__ slot, double* out) {
     const InstDesc& d = D[inst];
     const long long id = (long long)blockIdx.x * WG + threadIdx.x;
     if (id >= d.Np) return;
     const long long s = slot[id];
-    if (s >= d.ntiles * d.cap) return;  // a particle lost to an overflow
+    if (s >= d.ntiles * d.cap) return;
     PT px[3], pv[3];
     const PStore<DIM, PT> S{P.b, P.cs};
     const long long g = d.slot_off + s;
+    if (stats->dropped != 0ull) {
+        const uint32_t lt = (uint32_t)s / (uint32_t)d.cap, k = (uint32_t)s - lt * (uint32_t)d.cap;
+        if (k >= fill[d.tile_off + lt] || *S.id(g) != (uint32_t)id) return;
+    }
     if constexpr (S.F32 && WHAT == GATHER_POS) {
         const u32x4 a = *(const u32x4*)S.pos(0, g);
         px[0] = as_f(a.x); px[1] = as_f(a.y); px[2] = as_f(a.z);
@@ -256,8 +265,9 @@ template <typename PT>
 constexpr long long gather_inv_min() { return sizeof(PT) == 4 ? 1 << 18 : 1 << 24; }
 
 template <int DIM, typename PT>
-static void gather(const InstDesc* D, int inst, const InstDesc& d, PartBuf buf, const uint32_t* fill, double* pos_out,
-                   double* vel_out, int* cell_out, void* idle, long long t, int sub, hipStream_t s) {
+static void gather(const InstDesc* D, int inst, const InstDesc& d, PartBuf buf, const uint32_t* fill,
+                   const DevStats* stats, double* pos_out, double* vel_out, int* cell_out, void* idle, long long t,
+                   int sub, hipStream_t s) {
     const dim3 b(WG), tiles((unsigned)d.ntiles);
     if (cell_out) {
         hipLaunchKernelGGL((k_scatter<DIM, PT, GATHER_CELL>), tiles, b, 0, s, D, inst, buf, fill, nullptr, cell_out, t, sub);
@@ -268,19 +278,19 @@ static void gather(const InstDesc* D, int inst, const InstDesc& d, PartBuf buf, 
         const dim3 ids(nblk(d.Np));
         const uint32_t* slot = (const uint32_t*)idle;
         hipLaunchKernelGGL((k_scatter<DIM, PT, GATHER_INV>), dim3(xcd_grid(d.ntiles)), b, 0, s, D, inst, buf, fill, nullptr, (int*)idle, t, sub);
-        if (pos_out) hipLaunchKernelGGL((k_gather<DIM, PT, GATHER_POS>), ids, b, 0, s, D, inst, buf, slot, pos_out);
-        else hipLaunchKernelGGL((k_gather<DIM, PT, GATHER_VEL>), ids, b, 0, s, D, inst, buf, slot, vel_out);
+        if (pos_out) hipLaunchKernelGGL((k_gather<DIM, PT, GATHER_POS>), ids, b, 0, s, D, inst, buf, fill, stats, slot, pos_out);
+        else hipLaunchKernelGGL((k_gather<DIM, PT, GATHER_VEL>), ids, b, 0, s, D, inst, buf, fill, stats, slot, vel_out);
     }
 }
 
 hipError_t launch_gather(int dim, int part_fp, const InstDesc* D, int inst, const InstDesc& d, PartBuf buf,
-                         const uint32_t* fill, double* pos_out, double* vel_out, int* cell_out, void* idle, long long t,
-                         int sub, hipStream_t s) {
+                         const uint32_t* fill, const DevStats* stats, double* pos_out, double* vel_out, int* cell_out,
+                         void* idle, long long t, int sub, hipStream_t s) {
     if (d.ntiles <= 0) return hipSuccess;
-    if (dim == 2 && part_fp == 64) gather<2, double>(D, inst, d, buf, fill, pos_out, vel_out, cell_out, idle, t, sub, s);
-    else if (dim == 2) gather<2, float>(D, inst, d, buf, fill, pos_out, vel_out, cell_out, idle, t, sub, s);
-    else if (part_fp == 64) gather<3, double>(D, inst, d, buf, fill, pos_out, vel_out, cell_out, idle, t, sub, s);
-    else gather<3, float>(D, inst, d, buf, fill, pos_out, vel_out, cell_out, idle, t, sub, s);
+    if (dim == 2 && part_fp == 64) gather<2, double>(D, inst, d, buf, fill, stats, pos_out, vel_out, cell_out, idle, t, sub, s);
+    else if (dim == 2) gather<2, float>(D, inst, d, buf, fill, stats, pos_out, vel_out, cell_out, idle, t, sub, s);
+    else if (part_fp == 64) gather<3, double>(D, inst, d, buf, fill, stats, pos_out, vel_out, cell_out, idle, t, sub, s);
+    else gather<3, float>(D, inst, d, buf, fill, stats, pos_out, vel_out, cell_out, idle, t, sub, s);
     return hipGetLastError();
 }
 

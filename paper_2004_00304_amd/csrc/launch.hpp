@@ -64,10 +64,10 @@ hipError_t launch_fill_sequential(const InstDesc* D, int n_inst, long long tiles
                                   uint32_t* fill_other, hipStream_t s);
 // Particle state of one instance (d: its descriptor on the host) by id: one of
 // pos_out, vel_out ([dim][Np]) and cell_out.  idle: the particle buffer not in
-// use, overwritten.
+// use, overwritten.  Ids lost to tile overflows (stats->dropped) are left out.
 hipError_t launch_gather(int dim, int part_fp, const InstDesc* D, int inst, const InstDesc& d, PartBuf buf,
-                         const uint32_t* fill, double* pos_out, double* vel_out, int* cell_out, void* idle, long long t,
-                         int sub, hipStream_t s);
+                         const uint32_t* fill, const DevStats* stats, double* pos_out, double* vel_out, int* cell_out,
+                         void* idle, long long t, int sub, hipStream_t s);
 // Covers `slots` = ntiles * cap of that instance.
 hipError_t launch_cell_count(int dim, int part_fp, const InstDesc* D, int inst, PartBuf buf, const uint32_t* fill,
                              int* count_out, long long slots, long long t, int sub, hipStream_t s);
