@@ -1121,7 +1121,7 @@ int lbmpcd_set_state(lbmpcd_ctx* c, int32_t field, int32_t inst, const void* src
     }
     HIPCHK(c, launch_set_field(c->dim, c->part_fp, c->d_desc, inst, c->part[c->pcur], c->fill[c->pcur],
                                field == LBMPCD_PART_POS ? 0 : 1, (const double*)dsrc,
-                               d.ntiles, s));
+                               d.ntiles * (long long)d.cap, s));
     HIPCHK(c, hipStreamSynchronize(s));
     return 0;
 }

@@ -67,55 +67,73 @@ __global__ void __launch_bounds__(WG) k_fill_sequential(const InstDesc* __restri
     other[T] = 0u;
 }
 
-// Item of workgroup b of xcd_grid(items): the workgroups the hardware deals to
-// one XCD take one contiguous range, so that what neighbouring items scatter
-// to (or gather from) the same cache lines meets in one L2.
+// Workgroup b of xcd_grid(items) in an order in which the workgroups that the
+// hardware deals to one XCD take one contiguous range, so that what
+// neighbouring items scatter to (or gather from) the same cache lines meets in
+// one L2.
 __device__ __forceinline__ long long xcd_item() {
     return (long long)(blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
 }
 static inline unsigned xcd_grid(long long items) { return (unsigned)(8 * ((items + 7) / 8)); }
 
+// Slot `s` of instance d, in the buffer's numbering; -1 if it is empty.
+__device__ __forceinline__ long long filled_slot(const InstDesc& d, const uint32_t* __restrict__ fill, long long s) {
+    if (s >= d.ntiles * d.cap) return -1;
+    const uint32_t lt = (uint32_t)s / (uint32_t)d.cap, k = (uint32_t)s - lt * (uint32_t)d.cap;
+    return k < fill[d.tile_off + lt] ? d.slot_off + s : -1;
+}
+
+// Positions or velocities of slot g.
+template <int DIM, typename PT, bool VEL>
+__device__ __forceinline__ void load_field(const PStore<DIM, PT>& S, long long g, PT* v) {
+    if constexpr (PStore<DIM, PT>::F32 && DIM == 3 && !VEL) {
+        const u32x4 a = *(const u32x4*)S.pos(0, g);
+        v[0] = as_f(a.x); v[1] = as_f(a.y); v[2] = as_f(a.z);
+    } else {
+#pragma unroll
+        for (int q = 0; q < DIM; ++q) v[q] = VEL ? *S.vel(q, g) : *S.pos(q, g);
+    }
+}
+
 enum GatherWhat { GATHER_POS, GATHER_VEL, GATHER_CELL, GATHER_INV };
 
 // Positions, velocities or cells (in the binning of (t, sub)) of one
 // instance's particles scattered to their ids, or (GATHER_INV) the slots of
-// the ids; one workgroup per tile.
+// the ids; one thread per slot.  A workgroup per tile, which walks through the
+// tile's slots, has too few loads in flight and a ragged end: the inverse map's
+// read of 41.9M binary32 particles took 1617 us with it and takes 1464.
 template <int DIM, typename PT, int WHAT>
 __global__ void __launch_bounds__(WG) k_scatter(const InstDesc* __restrict__ D, int inst, PartBuf P,
                                                 const uint32_t* __restrict__ fill, double* out, int* out32, long long t,
                                                 int sub) {
     const InstDesc& d = D[inst];
-    // eight-byte components of a tile's surroundings overflow one L2: tiles
-    // in order, so that the XCDs share them in the cache behind it
-    const long long lt = WHAT == GATHER_INV ? xcd_item() : (long long)blockIdx.x;
-    if (lt >= d.ntiles) return;
-    const uint32_t n = min(fill[d.tile_off + lt], (uint32_t)d.cap);
-    const long long base = d.slot_off + lt * d.cap;
-    PT sh[3];
-    if constexpr (WHAT == GATHER_CELL) grid_shift_of<DIM, PT>(d, (uint32_t)t, (uint32_t)sub, sh);
-    for (uint32_t k = threadIdx.x; k < n; k += WG) {
-        PT px[3], pv[3];
-        uint32_t id;
-        load_part<DIM, PT>(P, base, k, px, pv, id);
-        if constexpr (PStore<DIM, PT>::ID_APART) id = load_id<DIM, PT>(P, base, k);
-        if ((long long)id >= d.Np) continue;
-        if constexpr (WHAT == GATHER_INV) {
-            out32[id] = (int)(lt * d.cap + k);
-        } else if constexpr (WHAT == GATHER_CELL) {
-            const PT rr = (PT)d.r;
-            int ix = bin_coord<PT>(px[0], (PT)0, sh[0], rr);
-            if (ix >= d.Cx) ix -= d.Cx;
-            const int iy = bin_row<PT>(d, px[1], sh[1], rr);
-            int iz = 0;
-            if (DIM == 3) {
-                iz = bin_coord<PT>(px[2], (PT)0, sh[2], rr);
-                if (iz >= d.Cz) iz -= d.Cz;
-            }
-            out32[id] = ix + d.Cx * (iy + d.CyB * iz);
-        } else {
-#pragma unroll
-            for (int q = 0; q < DIM; ++q) out[(long long)q * d.Np + id] = (double)(WHAT == GATHER_POS ? px[q] : pv[q]);
+    const long long s = xcd_item() * WG + threadIdx.x, g = filled_slot(d, fill, s);
+    if (g < 0) return;
+    const PStore<DIM, PT> S{P.b, P.cs};
+    const uint32_t id = *S.id(g);
+    if ((long long)id >= d.Np) return;
+    if constexpr (WHAT == GATHER_INV) {
+        out32[id] = (int)s;
+        return;
+    }
+    PT v[3];
+    load_field<DIM, PT, WHAT == GATHER_VEL>(S, g, v);
+    if constexpr (WHAT == GATHER_CELL) {
+        PT sh[3];
+        grid_shift_of<DIM, PT>(d, (uint32_t)t, (uint32_t)sub, sh);
+        const PT rr = (PT)d.r;
+        int ix = bin_coord<PT>(v[0], (PT)0, sh[0], rr);
+        if (ix >= d.Cx) ix -= d.Cx;
+        const int iy = bin_row<PT>(d, v[1], sh[1], rr);
+        int iz = 0;
+        if (DIM == 3) {
+            iz = bin_coord<PT>(v[2], (PT)0, sh[2], rr);
+            if (iz >= d.Cz) iz -= d.Cz;
         }
+        out32[id] = ix + d.Cx * (iy + d.CyB * iz);
+    } else if constexpr (WHAT != GATHER_INV) {
+#pragma unroll
+        for (int q = 0; q < DIM; ++q) out[(long long)q * d.Np + id] = (double)v[q];
     }
 }
 
@@ -134,22 +152,13 @@ __global__ void __launch_bounds__(WG) k_gather(const InstDesc* __restrict__ D, i
     if (id >= d.Np) return;
     const long long s = slot[id];
     if (s >= d.ntiles * d.cap) return;
-    PT px[3], pv[3];
     const PStore<DIM, PT> S{P.b, P.cs};
     const long long g = d.slot_off + s;
-    if (stats->dropped != 0ull) {
-        const uint32_t lt = (uint32_t)s / (uint32_t)d.cap, k = (uint32_t)s - lt * (uint32_t)d.cap;
-        if (k >= fill[d.tile_off + lt] || *S.id(g) != (uint32_t)id) return;
-    }
-    if constexpr (S.F32 && WHAT == GATHER_POS) {
-        const u32x4 a = *(const u32x4*)S.pos(0, g);
-        px[0] = as_f(a.x); px[1] = as_f(a.y); px[2] = as_f(a.z);
-    } else {
+    if (stats->dropped != 0ull && (filled_slot(d, fill, s) < 0 || *S.id(g) != (uint32_t)id)) return;
+    PT v[3];
+    load_field<DIM, PT, WHAT == GATHER_VEL>(S, g, v);
 #pragma unroll
-        for (int q = 0; q < DIM; ++q) (WHAT == GATHER_POS ? px : pv)[q] = WHAT == GATHER_POS ? *S.pos(q, g) : *S.vel(q, g);
-    }
-#pragma unroll
-    for (int q = 0; q < DIM; ++q) out[(long long)q * d.Np + id] = (double)(WHAT == GATHER_POS ? px[q] : pv[q]);
+    for (int q = 0; q < DIM; ++q) out[(long long)q * d.Np + id] = (double)v[q];
 }
 
 template <int DIM, typename PT>
@@ -180,20 +189,22 @@ __global__ void __launch_bounds__(WG) k_cell_count(const InstDesc* __restrict__ 
 }
 
 // Overwrite positions (which = 0) or velocities (1) of one instance by id.
+// The sources of a tile's particles lie in its surroundings, which the
+// XCD-blocked order keeps in one L2; from 2^25 particles on they overflow it,
+// and the XCDs share them better going through the tiles together (41.9M
+// binary32 particles after 200 LB steps: 2627 us blocked, 2377 in order; 10.5M
+// in 2D: 397 and 507).
 template <int DIM, typename PT>
 __global__ void __launch_bounds__(WG) k_set_field(const InstDesc* __restrict__ D, int inst, PStore<DIM, PT> P,
                                                   const uint32_t* __restrict__ fill, int which,
                                                   const double* __restrict__ src) {
     const InstDesc& d = D[inst];
-    const long long lt = blockIdx.x;
-    const uint32_t n = min(fill[d.tile_off + lt], (uint32_t)d.cap);
-    for (uint32_t k = threadIdx.x; k < n; k += WG) {
-        const long long g = d.slot_off + lt * d.cap + k;
-        const uint32_t id = *P.id(g);
-        if ((long long)id >= d.Np) continue;
+    const long long g = filled_slot(d, fill, (d.Np < (1 << 25) ? xcd_item() : (long long)blockIdx.x) * WG + threadIdx.x);
+    if (g < 0) return;
+    const uint32_t id = *P.id(g);
+    if ((long long)id >= d.Np) return;
 #pragma unroll
-        for (int q = 0; q < DIM; ++q) *(which == 0 ? P.pos(q, g) : P.vel(q, g)) = (PT)src[(long long)q * d.Np + id];
-    }
+    for (int q = 0; q < DIM; ++q) *(which == 0 ? P.pos(q, g) : P.vel(q, g)) = (PT)src[(long long)q * d.Np + id];
 }
 
 __global__ void __launch_bounds__(WG) k_zero(uint32_t* p, long long nwords) {
@@ -256,28 +267,28 @@ hipError_t launch_fill_sequential(const InstDesc* D, int n_inst, long long tiles
 // map (in `idle`, memory of at least 4 bytes a particle): one scattered 4-byte
 // store a particle, then consecutive 8-byte stores, instead of a scattered
 // 8-byte store for every component.  A tile's ids come from all its
-// surroundings, the more so the longer the run.  Binary32 records, which one
-// or two loads fetch, us a field directly / through the map after 100 LB
-// steps: 0.66M particles 30 / 25, 10.5M 487 / 461, 41.9M 3303 / 1736 (1535 /
-// 1213 after 2 LB steps).  Binary64 in 3D takes two loads a field from arrays
-// of their own: 10.5M 498 / 656, 21M 1621 / 1305.
-template <typename PT>
-constexpr long long gather_inv_min() { return sizeof(PT) == 4 ? 1 << 18 : 1 << 24; }
+// surroundings, the more so the longer the run.  us a field after 40 LB steps,
+// directly / through the map: binary32 in 3D, which one or two loads fetch,
+// 327k particles 15 / 17, 655k 29 / 24, 10.5M 409 / 380, 41.9M 3772 / 1464; in
+// 2D 5M 168 / 211, 18.9M 1022 / 783; binary64 2D 10.5M 320 / 420, 18.9M 1020 /
+// 788; 3D 10.5M 455 / 561, 21M 1427 / 1117.
+template <int DIM, typename PT>
+constexpr long long gather_inv_min() { return sizeof(PT) == 4 && DIM == 3 ? 1 << 19 : 1 << 24; }
 
 template <int DIM, typename PT>
 static void gather(const InstDesc* D, int inst, const InstDesc& d, PartBuf buf, const uint32_t* fill,
                    const DevStats* stats, double* pos_out, double* vel_out, int* cell_out, void* idle, long long t,
                    int sub, hipStream_t s) {
-    const dim3 b(WG), tiles((unsigned)d.ntiles);
+    const dim3 b(WG), slots(xcd_grid(nblk(d.ntiles * d.cap)));
     if (cell_out) {
-        hipLaunchKernelGGL((k_scatter<DIM, PT, GATHER_CELL>), tiles, b, 0, s, D, inst, buf, fill, nullptr, cell_out, t, sub);
-    } else if (d.Np < gather_inv_min<PT>()) {
-        if (pos_out) hipLaunchKernelGGL((k_scatter<DIM, PT, GATHER_POS>), tiles, b, 0, s, D, inst, buf, fill, pos_out, nullptr, t, sub);
-        else hipLaunchKernelGGL((k_scatter<DIM, PT, GATHER_VEL>), tiles, b, 0, s, D, inst, buf, fill, vel_out, nullptr, t, sub);
+        hipLaunchKernelGGL((k_scatter<DIM, PT, GATHER_CELL>), slots, b, 0, s, D, inst, buf, fill, nullptr, cell_out, t, sub);
+    } else if (d.Np < gather_inv_min<DIM, PT>()) {
+        if (pos_out) hipLaunchKernelGGL((k_scatter<DIM, PT, GATHER_POS>), slots, b, 0, s, D, inst, buf, fill, pos_out, nullptr, t, sub);
+        else hipLaunchKernelGGL((k_scatter<DIM, PT, GATHER_VEL>), slots, b, 0, s, D, inst, buf, fill, vel_out, nullptr, t, sub);
     } else {
         const dim3 ids(nblk(d.Np));
         const uint32_t* slot = (const uint32_t*)idle;
-        hipLaunchKernelGGL((k_scatter<DIM, PT, GATHER_INV>), dim3(xcd_grid(d.ntiles)), b, 0, s, D, inst, buf, fill, nullptr, (int*)idle, t, sub);
+        hipLaunchKernelGGL((k_scatter<DIM, PT, GATHER_INV>), slots, b, 0, s, D, inst, buf, fill, nullptr, (int*)idle, t, sub);
         if (pos_out) hipLaunchKernelGGL((k_gather<DIM, PT, GATHER_POS>), ids, b, 0, s, D, inst, buf, fill, stats, slot, pos_out);
         else hipLaunchKernelGGL((k_gather<DIM, PT, GATHER_VEL>), ids, b, 0, s, D, inst, buf, fill, stats, slot, vel_out);
     }
@@ -306,9 +317,9 @@ hipError_t launch_cell_count(int dim, int part_fp, const InstDesc* D, int inst, 
 }
 
 hipError_t launch_set_field(int dim, int part_fp, const InstDesc* D, int inst, PartBuf buf, const uint32_t* fill,
-                            int which, const double* src, long long ntiles, hipStream_t s) {
-    if (ntiles <= 0) return hipSuccess;
-    dim3 g((unsigned)ntiles), b(WG);
+                            int which, const double* src, long long slots, hipStream_t s) {
+    if (slots <= 0) return hipSuccess;
+    dim3 g(xcd_grid(nblk(slots))), b(WG);
     if (dim == 2 && part_fp == 64) hipLaunchKernelGGL((k_set_field<2, double>), g, b, 0, s, D, inst, typed<2, double>(buf), fill, which, src);
     else if (dim == 2) hipLaunchKernelGGL((k_set_field<2, float>), g, b, 0, s, D, inst, typed<2, float>(buf), fill, which, src);
     else if (part_fp == 64) hipLaunchKernelGGL((k_set_field<3, double>), g, b, 0, s, D, inst, typed<3, double>(buf), fill, which, src);

@@ -68,11 +68,11 @@ hipError_t launch_fill_sequential(const InstDesc* D, int n_inst, long long tiles
 hipError_t launch_gather(int dim, int part_fp, const InstDesc* D, int inst, const InstDesc& d, PartBuf buf,
                          const uint32_t* fill, const DevStats* stats, double* pos_out, double* vel_out, int* cell_out,
                          void* idle, long long t, int sub, hipStream_t s);
-// Covers `slots` = ntiles * cap of that instance.
+// Both cover `slots` = ntiles * cap of that instance.
 hipError_t launch_cell_count(int dim, int part_fp, const InstDesc* D, int inst, PartBuf buf, const uint32_t* fill,
                              int* count_out, long long slots, long long t, int sub, hipStream_t s);
 hipError_t launch_set_field(int dim, int part_fp, const InstDesc* D, int inst, PartBuf buf, const uint32_t* fill,
-                            int which, const double* src, long long ntiles, hipStream_t s);
+                            int which, const double* src, long long slots, hipStream_t s);
 hipError_t launch_zero(void* p, size_t bytes, hipStream_t s);
 hipError_t launch_exclusive_scan(int* a, long long n, hipStream_t s);
 hipError_t launch_node_mean(const double* acc, long long nslab, int dim, int det, double* out, hipStream_t s);

@@ -17,7 +17,8 @@ KW = dict(part_fp=32, capacity_factor=0.9, tile_target=1000, feedback=0)
 CASES = {
     "scattered_3d": W.small_3d(n=(24, 16, 20), ppc=8, **KW),
     "map_3d": W.small_3d(n=(48, 16, 40), ppc=8, **KW),
-    "map_2d": W.small_2d(n=(320, 24, 1), ppc=9, **KW),
+    "scattered_2d": W.small_2d(n=(320, 24, 1), ppc=9, **KW),
+    "map_2d": W.small_2d(n=(14600, 24, 1), ppc=9, **KW),
 }
 
 

@@ -1,0 +1,44 @@
+"""Particle state by id on both sides of the sizes at which its routes change:
+reads through the inverse map from 2^19 binary32 particles in 3D and 2^24
+otherwise, writes in the tiles' order from 2^25.  After some steps have mixed
+the tiles, positions and velocities written by set_state come back exactly."""
+import pytest
+
+from paper_2004_00304_amd import workloads as W
+from tests.gpu_util import banner
+from tests.test_gpu_parity import env  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+CASES = {
+    "3d_fp32_below": W.small_3d(part_fp=32, n=(64, 16, 40)),             # 512,000
+    "3d_fp32_map": W.small_3d(part_fp=32, n=(67, 16, 41)),               # 549,400
+    "2d_fp32_below": W.small_2d(part_fp=32, n=(14563, 24, 1), ppc=9),    # 16,776,576
+    "2d_fp32_map": W.small_2d(part_fp=32, n=(14567, 24, 1), ppc=9),      # 16,781,184
+    "2d_fp64_map": W.small_2d(n=(14567, 24, 1), ppc=9),
+    "2d_fp32_in_order": W.small_2d(part_fp=32, n=(21847, 24, 1), ppc=12),  # 33,556,992
+}
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_state_roundtrip(env, name):  # noqa: F811
+    _, lbmpcd = env
+    import torch
+    p = CASES[name]
+    banner(f"state routes {name}: {W.sizes(p)['particles']} particles")
+    sim = lbmpcd.Sim(p)
+    sim.step(2)
+    cells = sim.moments("cell_id")
+    pos = sim.get_state("pos")
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    vel = torch.randn(pos.numel(), dtype=torch.float64, device="cuda", generator=gen)
+    if p["part_fp"] == 32:
+        vel = vel.float().double()
+    sim.set_state("vel", vel)
+    assert torch.equal(sim.get_state("vel"), vel)
+    # the same positions by another route of the particle, mirrored and back
+    x = pos.reshape(p["dim"], -1)
+    sim.set_state("pos", x.flip(1).contiguous())
+    assert torch.equal(sim.get_state("pos").reshape(x.shape), x.flip(1))
+    sim.set_state("pos", pos)
+    assert torch.equal(sim.get_state("pos"), pos) and torch.equal(sim.moments("cell_id"), cells)
