@@ -10,6 +10,8 @@
 // plain product on its own.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "common.hpp"
 #include "gelu.hpp"
 #include "launch.hpp"
@@ -508,9 +510,11 @@ static size_t train_carve(unsigned char* base, long long rows, TrainBufs& b) {
     auto take = [&](size_t bytes) { unsigned char* p = base + o; o += (bytes + 255) & ~(size_t)255; return p; };
     const long long tiles = (rows + 31) / 32;
     b.nkb = 2 * tiles;
-    b.chunk = 8;
-    while ((b.nkb + b.chunk - 1) / b.chunk > 64) b.chunk += 2;
+    b.chunk = std::max(8LL, 2 * ((b.nkb + 127) / 128));  // at most 64 splits
     b.S = (int)((b.nkb + b.chunk - 1) / b.chunk);
+    // longer chunks make fewer splits (64 at 8,192 rows, 52 just above): room
+    // for as many as any smaller batch has, so that scratch serves fewer rows too
+    const long long splits = std::min(64LL, (b.nkb + 7) / 8);
     b.Xt = (uint16_t*)take((size_t)b.nkb * NFP * 32);
     for (int l = 0; l < 3; ++l) {
         b.Ht[l] = (uint16_t*)take((size_t)b.nkb * NH * 32);
@@ -518,7 +522,7 @@ static size_t train_carve(unsigned char* base, long long rows, TrainBufs& b) {
     }
     b.dYt = (uint16_t*)take((size_t)b.nkb * 16 * 32);
     b.db = (float*)take((size_t)tiles * NBIAS * 4);
-    b.part = (float*)take((size_t)b.S * NPARAM * 4);
+    b.part = (float*)take((size_t)splits * NPARAM * 4);
     return o;
 }
 
