@@ -150,8 +150,11 @@ typedef struct lbmpcd_params {
     int32_t tile[3];       /* particle tile in cells per axis (powers of two); 0 = from tile_target */
     double capacity_factor;/* tile capacity / expected occupancy; 0 = default 1.3 */
     int32_t tile_target;   /* expected particles per tile when tile[] is 0; 0 = default: 1280,
-                              and less where the context's channels would make fewer than
-                              2560 such tiles (640; in 2D below 512 320, below 128 160) */
+                              and with wg_threads 0 or 256 less where the context's channels
+                              would make fewer than 2560 such tiles (640; in 2D below 512
+                              320, below 128 160; binary32 particles in 2D keep 1280 from
+                              1536 tiles on with SRD, from 384 on with the Chapman-Enskog
+                              exchange, with both that and MPCD-AT from 1152 on) */
     int32_t wg_threads;    /* particle kernel workgroup: 128, 256 or 512 threads; 0 = 256,
                               or 512 for binary64 particles in tiles of over 1024 slots
                               unless the six-slot form applies.  Six-slot form: at 256

@@ -138,17 +138,33 @@ int ilog2(int v) {
 // barriers and tables best, but up to 1280 workgroups are resident at once
 // (five per CU), and a grid of fewer tiles leaves CUs idle while each tile
 // takes its full latency: smaller grids take smaller tiles.  Coupled step, us,
-// tiles of 1280 / the rule's: 2D channel (66 tiles of 1280) 69.1 / 51.2 at 160,
-// four times as long (264) 86.6 / 76.7 at 320; 3D slab of 1.8M binary32
-// particles (1,512) 237 / 216 at 640; 3D channel cut by 64 (2,200) 265 / 259.
+// tiles of 1280 / the rule's: 2D channel (68 tiles of 1280) 69.1 / 51.2 at 160,
+// four times as long (272) 86.6 / 76.7 at 320, 16 times (1,088) 184 / 174 at
+// 640, 32 times (2,176) 295 / 273, with MPCD-AT 348 / 309; 3D slab of 1.8M
+// binary32 particles (1,512) 237 / 216 at 640; 3D channel cut by 64 (2,200)
+// 265 / 259, in binary64 371 / 352, with MPCD-AT 440 / 394.
 // The next larger ones gain nothing: eight channels of the ensemble (3,150)
 // 409 / 419, 3D channel cut by 16 (8,700) 717 / 825.  In 3D, where a smaller
 // tile has more surface, 640 serves all grids below (168 tiles: 111.7 / 84.3,
 // 75.4 at 320; 693 tiles: 153 / 128, 144 at 320).
+// Binary32 in 2D, whose particles cost least beside a tile's own latency,
+// takes full tiles earlier with SRD, and with the Chapman-Enskog exchange,
+// whose waves are fewer, from the grids on where 320 would end (1280 / 640, SRD:
+// 1,360 tiles 177 / 174, 1,904 210 / 220; exchange: 408 tiles 122 / 129, 2,176
+// 332 / 381; with MPCD-AT as well: 1,088 tiles 238 / 233, 1,224 248 / 267;
+// MPCD-AT alone: 2,448 tiles 333 / 306).  A caller's 512 threads (or 128) want
+// a full tile on every grid: 512 at 640 lose up to 27 % (2D binary32, 272
+// tiles 77.7 / 99.0).
 constexpr int TILE_TARGET = 1280;
-int tile_target_for(int dim, long long tiles_of_1280) {
-    if (tiles_of_1280 >= 2560) return TILE_TARGET;
-    return dim == 3 || tiles_of_1280 >= 512 ? 640 : tiles_of_1280 >= 128 ? 320 : 160;
+int tile_target_for(const lbmpcd_params& p, long long tiles_of_1280) {
+    if (p.wg_threads != 0 && p.wg_threads != 256) return TILE_TARGET;
+    long long full = 2560;
+    if (p.dim == 2 && p.part_fp == 32) {
+        if (p.reinject) full = p.collision ? 1152 : 384;
+        else if (!p.collision) full = 1536;
+    }
+    if (tiles_of_1280 >= full) return TILE_TARGET;
+    return p.dim == 3 || tiles_of_1280 >= 512 ? 640 : tiles_of_1280 >= 128 ? 320 : 160;
 }
 
 int choose_tile(const lbmpcd_params& p, int target_default, Geometry& g, std::string& msg) {
@@ -380,7 +396,7 @@ int context_target(const lbmpcd_params* p, int n) {
         if (geometry(p[i], g, msg)) return TILE_TARGET;
         tiles += g.ntiles;
     }
-    return tile_target_for(p[0].dim, tiles);
+    return tile_target_for(p[0], tiles);
 }
 
 int build(const lbmpcd_params* p, int n, std::vector<InstDesc>& D, Layout& L, long long tot[7], std::string& msg) {
@@ -1189,7 +1205,7 @@ int lbmpcd_autotune(const lbmpcd_params* p, int32_t n_inst, void* dev_workspace,
     }
     static const int targets[] = {160, 320, 640, 1280};
     std::vector<lbmpcd_params> q0(p, p + n_inst);
-    for (auto& x : q0) x.tile_target = 0;
+    for (auto& x : q0) x.tile_target = x.wg_threads = 0;
     const int tt_default = context_target(q0.data(), n_inst);
     static const int wgs[] = {256, 512};
     std::vector<lbmpcd_params> q(p, p + n_inst);
