@@ -246,11 +246,19 @@ static_assert(4 * (4 + 3 * NHASH + 2) <= (int)LDS_HDR, "LDS header too small");
 // kernel spills at four (128 VGPRs) and runs faster at three (on MI355X:
 // 3.45 against 3.49 ms per MPCD step of the 3D channel with SRD, 4.93 against
 // 5.78 with MPCD-AT, 4.70 against 7.3 with the Chapman-Enskog exchange); with
-// binary64 particles (the batched 2D ensemble) four is as fast.  Six binary32
-// particles per thread fit five waves with SRD and four with MPCD-AT without
-// spilling; the Chapman-Enskog modes stay at three.
-template <typename PT, int MODE, int PPT>
+// binary64 particles (the batched 2D ensemble) four is as fast, but for eight
+// per thread and for six with MPCD-AT, which spill up to 254 registers at four
+// and none to 19 at three (coupled step, 4,352 tiles in 2D: MPCD-AT 0.782 ->
+// 0.622 ms, SRD with 128 threads 0.888 -> 0.573; 8,700 in 3D: MPCD-AT 1.583 ->
+// 1.319), and in 3D for eight per thread with the Chapman-Enskog exchange,
+// which spill up to 229 at three and none at two (2.49 -> 1.56 ms with 128
+// threads; in 2D two is slower on small grids).  Six binary32 particles per
+// thread fit five waves with SRD and four with MPCD-AT without spilling; the
+// Chapman-Enskog modes stay at three.
+template <int DIM, typename PT, int MODE, int PPT>
 constexpr int particle_waves() {
+    if (DIM == 3 && sizeof(PT) == 8 && PPT == 8 && (MODE & 8)) return 2;
+    if (sizeof(PT) == 8 && (PPT == 8 || (PPT == 6 && (MODE & 4)))) return 3;
     if (PPT == 6 && sizeof(PT) == 4) return (MODE & 8) ? 3 : (MODE & 4) ? 4 : 5;
     return (sizeof(PT) == 4 || (MODE & 8) != 0) ? 3 : 4;
 }
@@ -1024,7 +1032,7 @@ __device__ __forceinline__ void particle_tile(const PArgs<PT>& A, long long T, u
 
 // One workgroup per tile.
 template <int DIM, typename PT, int NT, int PPT, int MODE>
-__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(particle_waves<PT, MODE, PPT>())))
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(particle_waves<DIM, PT, MODE, PPT>())))
 k_particles(PArgs<PT> A) {
     extern __shared__ __align__(16) unsigned char smem[];
     // Workgroups are dealt to the eight XCDs in turn.  In the XCD-blocked
@@ -1044,7 +1052,7 @@ k_particles(PArgs<PT> A) {
 // kernel of its own, so that the loop does not weigh on the register
 // allocation of the one-tile kernel.
 template <int DIM, typename PT, int NT, int PPT, int MODE>
-__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(particle_waves<PT, MODE, PPT>())))
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(particle_waves<DIM, PT, MODE, PPT>())))
 k_particles_ovf(PArgs<PT> A) {
     extern __shared__ __align__(16) unsigned char smem[];
     const uint32_t cnt = A.ovf[0];
