@@ -58,6 +58,7 @@ struct lbmpcd_ctx {
     int coll_bit = 0;             // 4 for the MPCD-AT collision (particle kernel mode bit)
     int ce_bit = 0;               // 8 for the Chapman-Enskog exchange (particle kernel mode bit)
     int det_bit = 0;              // 16 for the deterministic mode (particle kernel mode bit)
+    int reps = 0;                 // some channel's cells have replicated sums
     int xcd_blocked = 1;          // XCD-blocked tile order of the particle kernel
     long long t = 0;
     bool pending = false, sampling = false, any_feedback = false;
@@ -586,7 +587,7 @@ int finalize(lbmpcd_ctx* c) {
     L.tile_inst = c->d_tile_inst; L.ufine = c->uf; L.tfine = c->tf; L.acc = c->acc; L.prof = c->prof;
     L.stats = c->stats; L.clock = c->clock; L.shifts = c->shifts;
     L.coll_dt = 0; L.coll_s = c->S - 1; L.str_s = 0;
-    L.diag_inst = -1; L.cell_vcm = nullptr; L.cap_max = c->cap_max; L.ovf = c->split_ok ? c->ovf : nullptr; L.exp_max = c->exp_max; L.wg_threads = c->wg_threads; L.xcd_blocked = c->xcd_blocked;
+    L.diag_inst = -1; L.cell_vcm = nullptr; L.cap_max = c->cap_max; L.ovf = c->split_ok ? c->ovf : nullptr; L.exp_max = c->exp_max; L.wg_threads = c->wg_threads; L.reps = c->reps; L.xcd_blocked = c->xcd_blocked;
     HIPCHK(c, launch_particles(L, c->stream));
     c->pending = false;
     return 0;
@@ -745,6 +746,7 @@ int lbmpcd_init(const lbmpcd_params* p, int32_t n_inst, void* dev_workspace, siz
         cap_max = std::max(cap_max, d.cap);
         c->exp_max = std::max(c->exp_max, d.ppc * d.nct);
         if (d.feedback) c->any_feedback = true;
+        if (d.lrep > 0) c->reps = 1;
     }
     c->cap_max = cap_max;
     c->wg_threads = p[0].wg_threads ? p[0].wg_threads
@@ -864,7 +866,7 @@ int enqueue_one_step(lbmpcd_ctx* c, hipStream_t s) {
                 // samples are taken in the last MPCD step of the LB step
                 L.do_fb = (c->any_feedback && sub == c->S - 1) ? 1 : 0;
                 L.do_prof = (c->sampling && sub == c->S - 1) ? 1 : 0;
-                L.diag_inst = -1; L.cell_vcm = nullptr; L.cap_max = c->cap_max; L.ovf = c->split_ok ? c->ovf : nullptr; L.exp_max = c->exp_max; L.wg_threads = c->wg_threads; L.xcd_blocked = c->xcd_blocked;
+                L.diag_inst = -1; L.cell_vcm = nullptr; L.cap_max = c->cap_max; L.ovf = c->split_ok ? c->ovf : nullptr; L.exp_max = c->exp_max; L.wg_threads = c->wg_threads; L.reps = c->reps; L.xcd_blocked = c->xcd_blocked;
                 HIPCHK(c, timed(c, 3, [&] { return launch_particles(L, s); }));
                 c->pcur ^= 1;
                 c->pending = true;
@@ -1043,7 +1045,7 @@ int produce(lbmpcd_ctx* c, int32_t field, int32_t inst, void* dst, size_t nbytes
             L.tile_inst = c->d_tile_inst; L.ufine = c->uf; L.tfine = c->tf; L.acc = c->acc; L.prof = c->prof;
             L.stats = c->stats; L.clock = c->clock; L.shifts = c->shifts; L.shifts = c->shifts;
             L.coll_dt = 0; L.coll_s = c->S - 1; L.str_s = 0;
-            L.diag_inst = inst; L.cell_vcm = (double*)dst; L.cap_max = c->cap_max; L.ovf = c->split_ok ? c->ovf : nullptr; L.exp_max = c->exp_max; L.wg_threads = c->wg_threads; L.xcd_blocked = c->xcd_blocked;
+            L.diag_inst = inst; L.cell_vcm = (double*)dst; L.cap_max = c->cap_max; L.ovf = c->split_ok ? c->ovf : nullptr; L.exp_max = c->exp_max; L.wg_threads = c->wg_threads; L.reps = c->reps; L.xcd_blocked = c->xcd_blocked;
             HIPCHK(c, launch_particles(L, s));
             return 0;
         }

@@ -50,6 +50,7 @@ struct ParticleLaunch {
     double* cell_vcm;             // [dim][ncells] or null
     int cap_max;                  // largest tile capacity
     int wg_threads;               // 256 or 512 threads per workgroup (0: 256)
+    int reps;                     // 1: some channel's cells have replicated sums (InstDesc::lrep)
     int xcd_blocked;              // 1: each XCD's workgroups take a contiguous range of tiles
     uint32_t* ovf;                // [2 + tiles] overflow list of a two-pass launch (zero-initialised), or
                                   // null: the context does not take the two-pass form
