@@ -571,12 +571,10 @@ __device__ __forceinline__ void particle_tile(const PArgs<PT>& A, long long T, u
         }
         if constexpr (!STREAM) {
             // collision only: velocities go back to their slots
-            const PStore<DIM, PT> out{A.out.b, A.out.cs};
 #pragma unroll
             for (int k = 0; k < PPT; ++k) {
                 if (!valid[k]) continue;
-#pragma unroll
-                for (int q = 0; q < DIM; ++q) *out.vel(q, base + tid + k * NT) = pv[k][q];
+                store_vel<DIM, PT>(A.out, base + tid + k * NT, px[k], pv[k]);
             }
             if (tid == 0 && wstat[1]) atomicAdd(&A.stats->misplaced, (unsigned long long)wstat[1]);
             return;

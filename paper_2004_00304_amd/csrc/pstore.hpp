@@ -126,4 +126,23 @@ __device__ __forceinline__ void store_part(const PartBuf& B, long long off, uint
     }
 }
 
+// Writes the velocity of slot g, whose position px it leaves as it is.  Where a
+// vector holds both, it is written whole: of every second half alone, a
+// collision without streaming took 423 us for 21M binary64 particles in 3D
+// instead of 352, and 46.9 instead of 44.2 for 5.2M binary32 in 2D.
+template <int DIM, typename PT>
+__device__ __forceinline__ void store_vel(const PartBuf& B, long long g, const PT* px, const PT* pv) {
+    using S = PStore<DIM, PT>;
+    unsigned char* a = B.b + g * 16;
+    if constexpr (S::F32) {
+        if constexpr (DIM == 3) *(F3*)(B.b + B.cs + g * 12) = F3{pv[0], pv[1], pv[2]};
+        else *(u32x4*)a = u32x4{__float_as_uint(px[0]), __float_as_uint(px[1]), __float_as_uint(pv[0]), __float_as_uint(pv[1])};
+    } else if constexpr (DIM == 3) {
+        *(double2*)(a + B.cs) = double2{px[2], pv[0]};
+        *(double2*)(a + 2 * B.cs) = double2{pv[1], pv[2]};
+    } else {
+        *(double2*)(a + B.cs) = double2{pv[0], pv[1]};
+    }
+}
+
 }  // namespace lbmpcd
