@@ -42,3 +42,18 @@ def test_state_roundtrip(env, name):  # noqa: F811
     assert torch.equal(sim.get_state("pos").reshape(x.shape), x.flip(1))
     sim.set_state("pos", pos)
     assert torch.equal(sim.get_state("pos"), pos) and torch.equal(sim.moments("cell_id"), cells)
+
+
+def test_second_channel_of_a_batch(env):  # noqa: F811
+    """The map of a channel whose slots do not start the buffer."""
+    _, lbmpcd = env
+    import torch
+    ps = [W.small_3d(part_fp=32, n=(20 + 3 * i, 16, 10 + i), instance=i) for i in range(2)] + [CASES["3d_fp32_map"]]
+    sim = lbmpcd.Sim(ps)
+    sim.step(2)
+    gen = torch.Generator(device="cuda").manual_seed(6)
+    want = [torch.randn(3 * W.sizes(p)["particles"], device="cuda", generator=gen).double() for p in ps]
+    for i, v in enumerate(want):
+        sim.set_state("vel", v, inst=i)
+    for i in (2, 0, 1, 2):
+        assert torch.equal(sim.get_state("vel", inst=i), want[i]), i
