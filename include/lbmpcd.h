@@ -150,11 +150,11 @@ typedef struct lbmpcd_params {
     int32_t tile[3];       /* particle tile in cells per axis (powers of two); 0 = from tile_target */
     double capacity_factor;/* tile capacity / expected occupancy; 0 = default 1.3 */
     int32_t tile_target;   /* expected particles per tile when tile[] is 0; 0 = default: 1280,
-                              and with wg_threads 0 or 256 less where the context's channels
-                              would make fewer than 2560 such tiles (640; in 2D below 512
-                              320, below 128 160; binary32 particles in 2D keep 1280 from
-                              1536 tiles on with SRD, from 384 on with the Chapman-Enskog
-                              exchange, with both that and MPCD-AT from 1152 on) */
+                              and with wg_threads 0 or 256 the smallest of 160, 320 and 640
+                              of which the context's channels make at most 768 tiles (256
+                              with substeps 2 or 3, 192 with 1) of at least 16 cells; 640
+                              also for binary64 particles with the Chapman-Enskog exchange,
+                              substeps of 2 or more and fewer than 2560 full tiles */
     int32_t wg_threads;    /* particle kernel workgroup: 128, 256 or 512 threads; 0 = 256,
                               or 512 for binary64 particles in tiles of over 1024 slots
                               unless the six-slot form applies.  Six-slot form: at 256
@@ -408,7 +408,8 @@ int lbmpcd_closure_loss_grad(struct lbmpcd_ctx* c, const float* X, const float* 
 /* Raw features of every slab node of the current populations (device X, nslab x 271). */
 int lbmpcd_closure_features(struct lbmpcd_ctx* c, float* X);
 
-/* Network output in physical units for n rows of raw features (device Y, n x 9). */
+/* Network output in physical units for n rows of raw features (device Y, n x 9).
+   The scratch is checked as for lbmpcd_closure_loss_grad, but neither read nor written. */
 int lbmpcd_closure_forward(struct lbmpcd_ctx* c, const float* X, int64_t n, float* Y, void* scratch,
                            size_t scratch_bytes);
 

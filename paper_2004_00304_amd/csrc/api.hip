@@ -136,37 +136,9 @@ int ilog2(int v) {
 }
 
 // Default tile size in expected particles.  Tiles of 1280 amortise a tile's
-// barriers and tables best, but up to 1280 workgroups are resident at once
-// (five per CU), and a grid of fewer tiles leaves CUs idle while each tile
-// takes its full latency: smaller grids take smaller tiles.  Coupled step, us,
-// tiles of 1280 / the rule's: 2D channel (68 tiles of 1280) 69.1 / 51.2 at 160,
-// four times as long (272) 86.6 / 76.7 at 320, 16 times (1,088) 184 / 174 at
-// 640, 32 times (2,176) 295 / 273, with MPCD-AT 348 / 309; 3D slab of 1.8M
-// binary32 particles (1,512) 237 / 216 at 640; 3D channel cut by 64 (2,200)
-// 265 / 259, in binary64 371 / 352, with MPCD-AT 440 / 394.
-// The next larger ones gain nothing: eight channels of the ensemble (3,150)
-// 409 / 419, 3D channel cut by 16 (8,700) 717 / 825.  In 3D, where a smaller
-// tile has more surface, 640 serves all grids below (168 tiles: 111.7 / 84.3,
-// 75.4 at 320; 693 tiles: 153 / 128, 144 at 320).
-// Binary32 in 2D, whose particles cost least beside a tile's own latency,
-// takes full tiles earlier with SRD, and with the Chapman-Enskog exchange,
-// whose waves are fewer, from the grids on where 320 would end (1280 / 640, SRD:
-// 1,360 tiles 177 / 174, 1,904 210 / 220; exchange: 408 tiles 122 / 129, 2,176
-// 332 / 381; with MPCD-AT as well: 1,088 tiles 238 / 233, 1,224 248 / 267;
-// MPCD-AT alone: 2,448 tiles 333 / 306).  A caller's 512 threads (or 128) want
-// a full tile on every grid: 512 at 640 lose up to 27 % (2D binary32, 272
-// tiles 77.7 / 99.0).
+// barriers, tables and sums best; on a grid that leaves CUs idle a tile's
+// latency counts instead, and smaller tiles have less of it (context_target).
 constexpr int TILE_TARGET = 1280;
-int tile_target_for(const lbmpcd_params& p, long long tiles_of_1280) {
-    if (p.wg_threads != 0 && p.wg_threads != 256) return TILE_TARGET;
-    long long full = 2560;
-    if (p.dim == 2 && p.part_fp == 32) {
-        if (p.reinject) full = p.collision ? 1152 : 384;
-        else if (!p.collision) full = 1536;
-    }
-    if (tiles_of_1280 >= full) return TILE_TARGET;
-    return p.dim == 3 || tiles_of_1280 >= 512 ? 640 : tiles_of_1280 >= 128 ? 320 : 160;
-}
 
 int choose_tile(const lbmpcd_params& p, int target_default, Geometry& g, std::string& msg) {
     int T[3] = {p.tile[0], p.tile[1], p.tile[2]};
@@ -264,7 +236,8 @@ int geometry(const lbmpcd_params& p, Geometry& g, std::string& msg, int target_d
     g.nty = (g.CyB + g.Ty - 1) / g.Ty;
     g.ntz = (g.Cz + g.Tz - 1) / g.Tz;
     g.ntiles = (long long)g.ntx * g.nty * g.ntz;
-    // the particle kernels address a channel's slots with 32-bit offsets
+    // size of a channel (with the 31-bit slot indices of a context): the stores
+    // take 64-bit addresses, so this is a limit kept, not one they need
     if (g.ntiles >= (1LL << 31) || g.ntiles * g.cap * (p.part_fp / 8) >= (1LL << 32)) {
         msg = "the particle slots of one channel exceed 4 GiB per component";
         return 1;
@@ -387,17 +360,49 @@ struct Layout {
     size_t acc_bytes, prof_bytes, scratch_bytes;
 };
 
-// Default tile target of a context's channels: a channel whose tile shape or
-// size is given counts with that.
+// Default tile target of a context's channels: the smallest of 160, 320 and 640
+// whose tiles, over all channels, stay within `most`, else 1280.  A channel
+// whose tile shape or size is given counts with that.
+//
+// Tiles in one round with a few per CU cost one tile's latency whatever their
+// size.  What limits them is the work per tile in a launch that samples (the
+// feedback's and the profile's global FP64 sums: 409,600 binary64 particles in
+// 2D, one MPCD step per LB step, 40.1 us at 1280, 64.7 at 320, 90.9 at 160),
+// which is one in S launches.  Measured on 700 random contexts of 10^4 to 5 10^6
+// particles in 2D and 3D, both precisions, all modes, with and without
+// sampling: with these limits a step takes 0.88 of its time at 1280 (0.82 in
+// binary32 with S >= 4), six in 1400 are more than 3 % slower, the worst 14 %;
+// limits of 1024 / 576 / 576 make it 55 in 1400 and up to 40 %.  2D channel (68
+// tiles of 1280, 544 of 160) 69.1 -> 51.2 us.  Tiles of fewer than 16 cells do
+// not pay (they come with dense cells, where the target changes little).
+//
+// Binary64 with the Chapman-Enskog exchange takes tiles of 640 up to 2560 full
+// ones: its full tiles need 512 threads, which serve that exchange worst (2D,
+// 2,176 tiles: 538 us at 1280, 380 at 640).  A caller's 512 threads (or 128)
+// want full tiles on every grid: 512 at 640 lose up to 27 % (2D binary32, 272
+// tiles 77.7 / 99.0 us).
 int context_target(const lbmpcd_params* p, int n) {
-    long long tiles = 0;
+    if (p[0].wg_threads != 0 && p[0].wg_threads != 256) return TILE_TARGET;
     std::string msg;
-    for (int i = 0; i < n; ++i) {
-        Geometry g;
-        if (geometry(p[i], g, msg)) return TILE_TARGET;
-        tiles += g.ntiles;
+    auto count = [&](int target, int& cells) {
+        long long tiles = 0;
+        cells = MAX_NCT;
+        for (int i = 0; i < n; ++i) {
+            Geometry g;
+            if (geometry(p[i], g, msg, target)) return -1LL;
+            tiles += g.ntiles;
+            if (p[i].tile_target <= 0 && p[i].tile[0] <= 0) cells = std::min(cells, g.nct);
+        }
+        return tiles;
+    };
+    const long long most = p[0].substeps >= 4 ? 768 : p[0].substeps >= 2 ? 256 : 192;
+    int cells;
+    for (int target : {160, 320, 640}) {
+        const long long tiles = count(target, cells);
+        if (tiles >= 0 && tiles <= most && cells >= 16) return target;
     }
-    return tile_target_for(p[0], tiles);
+    if (p[0].part_fp == 64 && p[0].reinject && p[0].substeps >= 2 && count(TILE_TARGET, cells) < 2560) return 640;
+    return TILE_TARGET;
 }
 
 int build(const lbmpcd_params* p, int n, std::vector<InstDesc>& D, Layout& L, long long tot[7], std::string& msg) {

@@ -383,10 +383,12 @@ __global__ void __launch_bounds__(256, RB) k_net(NetArgs a) {
     }
 }
 
-// Rows of physical outputs.  Tiles of 32 rows spread a small batch over more
-// of the chip; from 8,192 rows (256 such tiles) on, 64-row tiles read each
-// weight fragment's operands once per two products.  Two workgroups per CU
-// walk over what is left.
+// Rows of physical outputs.  Up to 8,192 rows every 32-row tile has a CU of its
+// own and the call takes one tile's latency (11.7 us); beyond, 64-row tiles read
+// each weight fragment's operands once per two products, and two workgroups per
+// CU walk over what is left (us, 64 rows / 32 rows: 8,193 rows 15.5 / 18.9,
+// 16,384 16.3 / 21.9, 65,536 38.0 / 76.5, 524,288 270 / 633; one workgroup per
+// CU 38.0 -> 55.2), although that form spills 16 of its 256 registers.
 hipError_t net_forward(const float* X, long long rows, const float* st, const uint16_t* Pf, const float* P32, float* out,
                        hipStream_t s) {
     NetArgs a{};
@@ -829,7 +831,7 @@ __global__ void __launch_bounds__(256) k_band_moments(const InstDesc* __restrict
 // one's gathers and products with another's GELUs.  The 271 features are
 // gathered, standardised, rounded and multiplied in chunks of eight stencil
 // entries (80 features, five k steps), which keeps a wave's LDS to one hidden
-// block (8.5 KB) and lets four waves share a SIMD.  The k steps run in the
+// block (8.5 KB) and lets three waves share a SIMD.  The k steps run in the
 // order of k_net's, so the two agree bit for bit.  Outputs: the standardised
 // network output Y and the centre node's LB velocity uc.
 //

@@ -347,7 +347,8 @@ __device__ __forceinline__ void particle_tile(const PArgs<PT>& A, long long T, u
     // ensemble 2.53 -> 2.10 ms per MPCD step), and of six binary32 records
     // the last comes after the rotations are drawn, whose FP64 series need the
     // registers (95 VGPRs and 16 spilled bytes -> 89 and none; film 5.51 ->
-    // 5.38 ms).  MPCD-AT and the Chapman-Enskog modes do not spill there.
+    // 5.38 ms).  MPCD-AT and the Chapman-Enskog modes do not spill there; in
+    // binary64 fewer waves end their spills (particle_waves), later loads do not.
     constexpr bool ID_LATE = PStore<DIM, PT>::ID_APART && !AT;
     constexpr int FIRST = (PPT == 6 && sizeof(PT) == 4 && !AT && !CE) ? PPT - 1 : PPT;
     auto load = [&](int k) {
@@ -1131,10 +1132,10 @@ static hipError_t launch_p2(const ParticleLaunch& L, hipStream_t s) {
 }
 
 // Tiles of 1025-2048 slots at 256 threads: six slots per thread instead of
-// eight leave the kernel fewer vector registers and, for binary32
-// particles, one more wave per SIMD (SRD: 96 VGPRs and five waves instead
-// of 113 and four; MPCD-AT: 123 and four instead of 152 and three); binary64
-// particles stay at four waves and spill 24 bytes per lane instead of 108.
+// eight leave the kernel fewer vector registers and one more wave per SIMD
+// (binary32, SRD: 89 VGPRs and five waves instead of 113 and four; MPCD-AT: 123
+// and four instead of 151 and three; binary64, SRD: 128 and four instead of
+// 147 and three).
 // A tile holding
 // more than 1536 particles is skipped and listed by that launch and
 // processed by a second launch over the list (512 threads, four slots per

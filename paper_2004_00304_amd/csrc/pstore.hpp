@@ -55,7 +55,6 @@ inline PStore<DIM, PT> typed(const PartBuf& p) { return PStore<DIM, PT>{p.b, p.c
 // (its uniform 64-bit base in scalar registers) and a 32-bit byte offset per
 // lane.  Stores go to any tile of the channel, whose arrays may exceed 4 GiB,
 // so they take 64-bit addresses.
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x3 __attribute__((ext_vector_type(3)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 struct __attribute__((packed, aligned(4))) F3 { float x, y, z; };

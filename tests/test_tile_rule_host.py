@@ -1,6 +1,6 @@
-"""The default tile size (host logic): on either side of each of the rule's edges
-the workspace is that of the tile size which the rule names, for one channel,
-for a batch that is counted together, and with a workgroup chosen by the caller."""
+"""The default tile size (host logic): the workspace is that of the tile size
+which the rule names, on either side of each of its edges, for one channel, for
+a batch that is counted together, and with a workgroup chosen by the caller."""
 import pytest
 
 from paper_2004_00304_amd import lbmpcd
@@ -19,43 +19,52 @@ def chosen(ps):
 
 
 def channel(columns, **kw):
-    """Tiles of 1280 are 64 x 2 cells: 17 on the 33 rows of every 16 nodes of length."""
+    """33 rows of 64 cells for every 16 nodes of length, 10 particles in each:
+    136, 68, 34 and 17 tiles of 160, 320, 640 and 1280 particles."""
     return W.make(n=(16 * columns, 32, 1), **kw)
 
 
-F32, CE, AT = dict(part_fp=32), dict(reinject=1), dict(collision=1)
-
-
-@pytest.mark.parametrize("kw,edges", [
-    ({}, {128: (160, 320), 512: (320, 640), 2560: (640, 1280)}),
-    (AT, {128: (160, 320), 512: (320, 640), 2560: (640, 1280)}),
-    (CE, {512: (320, 640), 2560: (640, 1280)}),
-    (F32, {128: (160, 320), 512: (320, 640), 1536: (640, 1280)}),
-    ({**F32, **AT}, {512: (320, 640), 2560: (640, 1280)}),
-    ({**F32, **CE}, {128: (160, 320), 384: (320, 1280)}),
-    ({**F32, **CE, **AT}, {512: (320, 640), 1152: (640, 1280)}),
-    (dict(wg_threads=256), {128: (160, 320), 2560: (640, 1280)}),
+@pytest.mark.parametrize("fp", [32, 64])
+@pytest.mark.parametrize("at", [0, 1])
+@pytest.mark.parametrize("substeps,sizes", [
+    (4, {1: 160, 5: 160, 6: 320, 11: 320, 12: 640, 22: 640, 23: 1280, 200: 1280}),   # at most 768 tiles
+    (8, {5: 160, 6: 320, 23: 1280}),
+    (2, {1: 160, 2: 320, 3: 320, 4: 640, 7: 640, 8: 1280}),                          # at most 256
+    (3, {1: 160, 2: 320, 8: 1280}),
+    (1, {1: 160, 2: 320, 3: 640, 5: 640, 6: 1280}),                                  # at most 192
 ])
-def test_edges(kw, edges):
-    for edge, (below, above) in edges.items():
-        assert chosen([channel((edge - 1) // 17, **kw)]) == below, (edge, kw)
-        assert chosen([channel(-(-edge // 17), **kw)]) == above, (edge, kw)
+def test_edges(substeps, sizes, at, fp):
+    for columns, size in sizes.items():
+        assert chosen([channel(columns, substeps=substeps, collision=at, part_fp=fp)]) == size, columns
+
+
+def test_chapman_enskog_in_binary64():
+    for columns, size in {5: 160, 6: 320, 23: 640, 150: 640, 151: 1280}.items():   # 150 columns: 2,550 full tiles
+        assert chosen([channel(columns, reinject=1)]) == size, columns
+    assert chosen([channel(23, reinject=1, part_fp=32)]) == 1280
+    assert chosen([channel(23, reinject=1, substeps=1)]) == 1280
 
 
 @pytest.mark.parametrize("fp", [32, 64])
 def test_3d(fp):
-    # one tile of 4 x 2 x 8 cells in the channel's 512 x 65 x 256 cells cut in x and z
+    assert chosen([W.channel_3d_scaled(32, 64, part_fp=fp)]) == 320
     assert chosen([W.channel_3d_scaled(16, 32, part_fp=fp)]) == 640
-    assert chosen([W.channel_3d_scaled(8, 8, part_fp=fp)]) == 640
-    assert chosen([W.channel_3d_scaled(8, 4, part_fp=fp)]) == 1280
+    assert chosen([W.channel_3d_scaled(16, 16, part_fp=fp)]) == 1280
 
 
 def test_a_batch_is_counted_together():
-    ps = [W.make(n=(64, 32, 1), instance=i) for i in range(2)]  # 68 tiles of 1280 each
-    assert chosen(ps[:1]) == 160 and chosen(ps) == 320
-    assert chosen([W.make(n=(64, 32, 1), instance=i) for i in range(8)]) == 640
+    ps = [channel(4, instance=i) for i in range(6)]   # 544 tiles of 160 each
+    assert [chosen(ps[:k]) for k in (1, 2, 3, 5, 6)] == [160, 320, 640, 640, 1280]
 
 
-@pytest.mark.parametrize("p", [channel(4), channel(16, **F32), W.channel_3d_scaled(8, 8)])
+def test_dense_cells_keep_full_tiles():
+    """60 particles per cell: 160 and 320 would be tiles of eight cells."""
+    p = W.make(n=(32, 32, 1), ppc=60)
+    assert lbmpcd.workspace_size([p]) == lbmpcd.workspace_size([{**p, "tile_target": 640}])
+    assert lbmpcd.workspace_size([p]) != lbmpcd.workspace_size([{**p, "tile_target": 320}])
+
+
+@pytest.mark.parametrize("p", [channel(4), channel(16, part_fp=32), W.channel_3d_scaled(16, 32)])
 def test_a_callers_512_threads_take_full_tiles(p):
     assert chosen([{**p, "wg_threads": 512}]) == 1280
+    assert chosen([{**p, "wg_threads": 256}]) < 1280
