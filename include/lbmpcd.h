@@ -152,7 +152,8 @@ typedef struct lbmpcd_params {
     int32_t tile_target;   /* expected particles per tile when tile[] is 0; 0 = default: 1280,
                               and with wg_threads 0 or 256 the smallest of 160, 320 and 640
                               of which the context's channels make at most 768 tiles (256
-                              with substeps 2 or 3, 192 with 1) of at least 16 cells; 640
+                              with substeps 2 or 3, 192 with 1) of at least 16 cells (in 3D
+                              with refine 1 only 640); 640 is taken
                               also for binary64 particles with the Chapman-Enskog exchange,
                               substeps of 2 or more and fewer than 2560 full tiles */
     int32_t wg_threads;    /* particle kernel workgroup: 128, 256 or 512 threads; 0 = 256,

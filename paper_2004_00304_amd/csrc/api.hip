@@ -374,7 +374,10 @@ struct Layout {
 // binary32 with S >= 4), six in 1400 are more than 3 % slower, the worst 14 %;
 // limits of 1024 / 576 / 576 make it 55 in 1400 and up to 40 %.  2D channel (68
 // tiles of 1280, 544 of 160) 69.1 -> 51.2 us.  Tiles of fewer than 16 cells do
-// not pay (they come with dense cells, where the target changes little).
+// not pay (they come with dense cells, where the target changes little).  In 3D
+// at r = 1 the sample window of tiles of 640 and more is larger than its table
+// and every feedback sample counts as a miss in STATS; smaller tiles would gain
+// 5 % and count others, so those grids keep 640.
 //
 // Binary64 with the Chapman-Enskog exchange takes tiles of 640 up to 2560 full
 // ones: its full tiles need 512 threads, which serve that exchange worst (2D,
@@ -397,7 +400,10 @@ int context_target(const lbmpcd_params* p, int n) {
     };
     const long long most = p[0].substeps >= 4 ? 768 : p[0].substeps >= 2 ? 256 : 192;
     int cells;
+    bool r1 = false;
+    for (int i = 0; i < n; ++i) r1 |= p[i].dim == 3 && p[i].refine == 1;
     for (int target : {160, 320, 640}) {
+        if (r1 && target < 640) continue;
         const long long tiles = count(target, cells);
         if (tiles >= 0 && tiles <= most && cells >= 16) return target;
     }

@@ -52,6 +52,11 @@ def test_3d(fp):
     assert chosen([W.channel_3d_scaled(16, 16, part_fp=fp)]) == 1280
 
 
+def test_3d_without_refinement():
+    assert chosen([W.small_3d(n=(48, 16, 40), refine=1, ppc=20)]) == 640
+    assert chosen([W.small_3d(n=(24, 16, 20), refine=2, ppc=10)]) == 320
+
+
 def test_a_batch_is_counted_together():
     ps = [channel(4, instance=i) for i in range(6)]   # 544 tiles of 160 each
     assert [chosen(ps[:k]) for k in (1, 2, 3, 5, 6)] == [160, 320, 640, 640, 1280]
