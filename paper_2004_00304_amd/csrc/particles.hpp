@@ -224,15 +224,16 @@ constexpr size_t LDS_HDR = 1088;  // >= 4 * (4 + 3 * NHASH + 2), a multiple of 1
 // Node sample window: NREP interleaved replicas of every bin (lane l adds into
 // replica l mod NREP), so that the lanes of a wave, which mostly sample the
 // same few nodes, spread their FP64 atomics over more banks.  Profile window:
-// a wave's particles lie in two or three fine rows, so every row has a slot per
-// lane (per pair of lanes in windows of more than eight rows), component by
-// component, and no two lanes of a wave meet on an address; with four
-// replicas per row five did (thin film, a sampling launch: 6.83 -> 6.66 ms;
-// without the barrier that the shared region saves every launch, 3D channel
-// step 12.55 -> 12.46 ms).
+// a wave's particles lie in two or three fine rows, so every row has WSLOTS
+// slots, component by component (lane l adds into slot l mod WSLOTS); with four
+// replicas per row and the region of its own that they had before, a sampling
+// launch of the thin film took 6.83 ms, with a slot per lane 6.66.  Sixteen, summed
+// by one thread per row and component, cost small tiles less than a slot per
+// lane summed by shuffles (binary32 in 2D, 12,700 tiles of 640 particles, a
+// sampled step 300 -> 283 us; film cut by 16, one MPCD step 1369 -> 1366).
 constexpr int NREP = 4;
-constexpr int PROF_SLOTS = 512;  // rows x slots per row of the profile window
-static_assert(MAX_WJ * 32 <= PROF_SLOTS, "profile window rows");
+constexpr int WSLOTS = 16;
+constexpr int PROF_SLOTS = MAX_WJ * WSLOTS;  // rows x slots per row of the profile window
 constexpr size_t LDS_WIN = ((size_t)MAX_WIN * NREP * 4 + (size_t)PROF_SLOTS * 4) * sizeof(double);
 // The exchange reads the LB velocity of a buffer particle's fine cell.  A
 // particle binned into shifted cell i (shift in [0, a)) sits in unshifted
@@ -603,7 +604,6 @@ __device__ __forceinline__ void particle_tile(const PArgs<PT>& A, long long T, u
         const bool win_ok = wnx * wny * wnz <= MAX_WIN;
         const int wj0 = (ty << d.lTy) - 2, wnj = d.Ty + 4;
         const bool wj_ok = wnj <= MAX_WJ;
-        const int wslots = wnj <= PROF_SLOTS / 64 ? 64 : 32;
         const int copy = (int)(lt % (uint32_t)NCOPY);
         // the collision's barriers cover the tables written at the start
         if constexpr (!COLL) __syncthreads();
@@ -791,7 +791,7 @@ __device__ __forceinline__ void particle_tile(const PArgs<PT>& A, long long T, u
             if (A.do_fb && win_ok)
                 for (int i = tid; i < wnx * wny * wnz * NREP * 4; i += NT) wacc[i] = 0.0;
             if (A.do_prof && wj_ok)
-                for (int i = tid; i < wnj * wslots * 4; i += NT) wprof[i] = 0.0;
+                for (int i = tid; i < wnj * WSLOTS * 4; i += NT) wprof[i] = 0.0;
             __syncthreads();
             const int wrep = 4 * (lane & (NREP - 1));
 #pragma unroll
@@ -829,7 +829,7 @@ __device__ __forceinline__ void particle_tile(const PArgs<PT>& A, long long T, u
                     if (wj_ok && aj >= 0 && aj < wnj) {
 #pragma unroll
                         for (int q = 0; q < DIM + 1; ++q)
-                            sum_lds<DET>(&wprof[(q * wnj + aj) * wslots + (lane & (wslots - 1))], vals[q]);
+                            sum_lds<DET>(&wprof[(q * wnj + aj) * WSLOTS + (lane & (WSLOTS - 1))], vals[q]);
                     } else {
                         double* gb = A.prof + (d.prof_off + (long long)copy * d.R + J) * 4;
 #pragma unroll
@@ -1000,24 +1000,20 @@ __device__ __forceinline__ void particle_tile(const PArgs<PT>& A, long long T, u
             }
         }
         if (A.do_prof && wj_ok) {
-            // 16 lanes per row and component; the four components of a row
+            // one thread per row and component; the four components of a row
             // leave in one instruction
-            for (int i = tid >> 4; i < wnj * 4; i += NT / 16) {
+            for (int i = tid; i < wnj * 4; i += NT) {
                 const int q = i & 3, row = i >> 2;
                 if (DIM == 2 && q == 3) continue;
-                const double* w = wprof + (q * wnj + row) * wslots;
+                const double* w = wprof + (q * wnj + row) * WSLOTS;
                 double sum = 0.0;
                 [[maybe_unused]] unsigned long long isum = 0ull;
-                for (int j = tid & 15; j < wslots; j += 16) {
+#pragma unroll
+                for (int j = 0; j < WSLOTS; ++j) {
                     if constexpr (DET) isum += ((const unsigned long long*)w)[j];
                     else sum += w[j];
                 }
-#pragma unroll
-                for (int o = 8; o > 0; o >>= 1) {
-                    if constexpr (DET) isum += __shfl_xor(isum, o);
-                    else sum += __shfl_xor(sum, o);
-                }
-                if ((tid & 15) != 0 || (DET ? isum == 0ull : sum == 0.0)) continue;
+                if (DET ? isum == 0ull : sum == 0.0) continue;
                 int J = wj0 + row;
                 if (J < 0) J += d.R; else if (J >= d.R) J -= d.R;
                 double* gb = A.prof + (d.prof_off + (long long)copy * d.R + J) * 4 + q;
