@@ -436,7 +436,7 @@ int build(const lbmpcd_params* p, int n, std::vector<InstDesc>& D, Layout& L, lo
         d.Tx = g.Tx; d.Ty = g.Ty; d.Tz = g.Tz; d.ntx = g.ntx; d.nty = g.nty; d.ntz = g.ntz;
         d.lTx = ilog2(g.Tx); d.lTy = ilog2(g.Ty); d.lTz = ilog2(g.Tz);
         d.lr = (p[i].refine & (p[i].refine - 1)) == 0 ? ilog2(p[i].refine) : -1;
-        d.lrep = g.nct <= 4 ? 5 : 0;
+        d.lrep = g.nct <= 4 ? 3 : 0;
         d.cap = g.cap; d.nct = g.nct; d.ntiles = g.ntiles; d.tile_off = tiles; d.slot_off = slots;
         d.by0 = g.by0; d.nyb = g.nyb; d.band_off = band; d.NB = g.NB; d.ufine_off = ufine;
         d.nslab = g.nslab; d.acc_off = slab; d.prof_off = prow;

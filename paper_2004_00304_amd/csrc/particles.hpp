@@ -287,12 +287,14 @@ __device__ __forceinline__ void particle_tile(const PArgs<PT>& A, long long T, u
     double* wacc = (double*)uni;                // [MAX_WIN][NREP][4] node sample window
     double* wprof = wacc + MAX_WIN * NREP * 4;  // [4][rows][slots] profile window
     // Cell sums: in tiles of at most four cells (hundreds of particles per
-    // cell, which 512 threads serve) every cell keeps 32 replicas, lane l
-    // adding into replica l mod 32, so that a cell's particles do not all meet
-    // on one address.  Coupled step of the paper's channels at 1,000 particles
-    // per cell, MPCD-AT: centre line 39.8 -> 35.4 us, near the wall 56.9 ->
-    // 50.9.  More cells per tile measure slower with replicas (2D channel with
-    // eight per cell 51.1 -> 52.9 us).
+    // cell, which 512 threads serve) every cell keeps eight replicas, lane l
+    // adding into replica l mod 8, so that a cell's particles do not all meet
+    // on one address.  Coupled step of the paper's channel (centre line, MPCD-AT,
+    // binary64) without, with eight and with 32: 1,000 particles per cell 40.2,
+    // 32.3 and 33.9 us, at 200 nodes' length 155, 109 and 119; 250 per cell, 1,000
+    // nodes 145, 137 and 151 (the 32 have to be summed).  More cells per tile
+    // measure slower with 32 replicas (2D channel with eight per cell 51.1 ->
+    // 52.9 us).
     uint32_t* ccnt = (uint32_t*)uni;                 // [MAX_NCT]
     double* csv = (double*)(uni + MAX_NCT * 4);      // [MAX_NCT][3]
     double* cvcm = csv + MAX_NCT * 3;                // [MAX_NCT][3]
