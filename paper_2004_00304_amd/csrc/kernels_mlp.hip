@@ -124,12 +124,6 @@ __device__ __forceinline__ void frag_store(uint16_t* Pf, long long i, uint16_t v
     }
 }
 
-// Clears the fragment arrays (their padding stays zero) before the first fill.
-__global__ void __launch_bounds__(256) k_frag_zero(uint16_t* Pf) {
-    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (i < NFRAG) Pf[i] = 0;
-}
-
 // ---------------------------------------------------------------------------
 // the network, forward and backward, on tiles of rows
 // ---------------------------------------------------------------------------
@@ -566,8 +560,7 @@ hipError_t net_gradient(const NetBatch& q, void* scratch, float* G, const AdamSt
 
 // Uniform(-a, a) weights with a = sqrt(6 / (fan_in + fan_out)) over the real
 // inputs (Glorot), zero biases, zero padding columns, zero Adam moments.
-__global__ void __launch_bounds__(256) k_mlp_init(float* P, uint16_t* Pf, float* m, float* v, uint32_t k0,
-                                                  uint32_t k1) {
+__global__ void __launch_bounds__(256) k_mlp_init(float* P, float* m, float* v, uint32_t k0, uint32_t k1) {
     const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
     if (i >= NPARAM) return;
     float w = 0.0f;
@@ -584,26 +577,39 @@ __global__ void __launch_bounds__(256) k_mlp_init(float* P, uint16_t* Pf, float*
         w = (float)((2.0 * u01(r.x, r.y) - 1.0) * a);
     }
     P[i] = w;
-    frag_store(Pf, i, to_bf16(w));
     m[i] = 0.0f;
     v[i] = 0.0f;
 }
 
-hipError_t mlp_init(float* P32, uint16_t* Pf, float* m, float* v, uint32_t k0, uint32_t k1, hipStream_t s) {
-    hipLaunchKernelGGL(k_frag_zero, dim3(nblk(NFRAG)), dim3(256), 0, s, Pf);
-    hipLaunchKernelGGL(k_mlp_init, dim3(nblk(NPARAM)), dim3(256), 0, s, P32, Pf, m, v, k0, k1);
-    return hipGetLastError();
-}
-
+// Every element of the fragment arrays from the parameters, the padding zero:
+// the inverse of frag_store's places.
 __global__ void __launch_bounds__(256) k_frag_fill(const float* P, uint16_t* Pf) {
     const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (i < NPARAM) frag_store(Pf, i, to_bf16(P[i]));
+    if (i >= NFRAG) return;
+    struct Part { long long at, w; int ncb, outs, ins; bool t; };
+    constexpr Part parts[7] = {{FRAG_L1, OFF_W1, 4, NH, NFP, false},  {FRAG_L2, OFF_W2, 4, NH, NH, false},
+                               {FRAG_L3, OFF_W3, 4, NH, NH, false},   {FRAG_L4, OFF_W4, 1, NOUT, NH, false},
+                               {TFRAG_L2, OFF_W2, 4, NH, NH, true},   {TFRAG_L3, OFF_W3, 4, NH, NH, true},
+                               {TFRAG_L4, OFF_W4, 4, NOUT, NH, true}};
+    Part q = parts[0];
+#pragma unroll
+    for (int l = 1; l < 7; ++l)
+        if (i >= parts[l].at) q = parts[l];
+    const int e = (int)(i - q.at), lane = (e >> 3) & 63, sb = e >> 9;
+    const int k = 16 * (sb / q.ncb) + 8 * (lane >> 5) + (e & 7), n = 32 * (sb % q.ncb) + (lane & 31);
+    const int o = q.t ? k : n, c = q.t ? n : k;
+    Pf[i] = o < q.outs ? to_bf16(P[q.w + (long long)o * q.ins + c]) : (uint16_t)0;
 }
 
 hipError_t mlp_refresh(const float* P32, uint16_t* Pf, hipStream_t s) {
-    hipLaunchKernelGGL(k_frag_zero, dim3(nblk(NFRAG)), dim3(256), 0, s, Pf);
-    hipLaunchKernelGGL(k_frag_fill, dim3(nblk(NPARAM)), dim3(256), 0, s, P32, Pf);
+    hipLaunchKernelGGL(k_frag_fill, dim3(nblk(NFRAG)), dim3(256), 0, s, P32, Pf);
     return hipGetLastError();
+}
+
+hipError_t mlp_init(float* P32, uint16_t* Pf, float* m, float* v, uint32_t k0, uint32_t k1, hipStream_t s) {
+    hipLaunchKernelGGL(k_mlp_init, dim3(nblk(NPARAM)), dim3(256), 0, s, P32, m, v, k0, k1);
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess ? mlp_refresh(P32, Pf, s) : e;
 }
 
 // ---------------------------------------------------------------------------
