@@ -140,9 +140,11 @@ int ilog2(int v) {
 // latency counts instead, and smaller tiles have less of it (context_target).
 constexpr int TILE_TARGET = 1280;
 
+bool tile_given(const lbmpcd_params& p) { return p.tile[0] > 0 && p.tile[1] > 0 && (p.dim == 2 || p.tile[2] > 0); }
+
 int choose_tile(const lbmpcd_params& p, int target_default, Geometry& g, std::string& msg) {
     int T[3] = {p.tile[0], p.tile[1], p.tile[2]};
-    if (T[0] <= 0 || T[1] <= 0 || (p.dim == 3 && T[2] <= 0)) {
+    if (!tile_given(p)) {
         const int per_tile = p.tile_target > 0 ? p.tile_target : target_default;
         int target = std::max(8, std::min(MAX_NCT, per_tile / std::max(1, p.ppc)));
         // shapes below 8 cells serve only dense cells (hundreds of particles
@@ -394,20 +396,22 @@ int context_target(const lbmpcd_params* p, int n) {
             Geometry g;
             if (geometry(p[i], g, msg, target)) return -1LL;
             tiles += g.ntiles;
-            if (p[i].tile_target <= 0 && p[i].tile[0] <= 0) cells = std::min(cells, g.nct);
+            if (p[i].tile_target <= 0 && !tile_given(p[i])) cells = std::min(cells, g.nct);
         }
         return tiles;
     };
     const long long most = p[0].substeps >= 4 ? 768 : p[0].substeps >= 2 ? 256 : 192;
     int cells;
+    long long tiles = -1;
     bool r1 = false;
     for (int i = 0; i < n; ++i) r1 |= p[i].dim == 3 && p[i].refine == 1;
     for (int target : {160, 320, 640}) {
         if (r1 && target < 640) continue;
-        const long long tiles = count(target, cells);
+        tiles = count(target, cells);
         if (tiles >= 0 && tiles <= most && cells >= 16) return target;
     }
-    if (p[0].part_fp == 64 && p[0].reinject && p[0].substeps >= 2 && count(TILE_TARGET, cells) < 2560) return 640;
+    if (tiles >= 0 && p[0].part_fp == 64 && p[0].reinject && p[0].substeps >= 2 && count(TILE_TARGET, cells) < 2560)
+        return 640;
     return TILE_TARGET;
 }
 
