@@ -843,7 +843,7 @@ __global__ void __launch_bounds__(256) k_band_moments(const InstDesc* __restrict
 //
 // What bounds it: the vector work of 384 GELUs and 271 features per node (the
 // matrix cores are busy a tenth of the time) and the loads' latency.  524,288
-// nodes: 219 us (328 TFLOP/s of network arithmetic); 334 us with all features
+// nodes: 194 us (370 TFLOP/s of network arithmetic); 334 us with all features
 // of 32 rows in LDS (two waves per SIMD, a barrier per layer), 370 us with a
 // wave per 32 columns and its weights in registers (two waves per SIMD, five
 // barriers per tile).  Three waves per SIMD: at four 21 registers spill (235
